@@ -11,7 +11,8 @@ this way.
     tunable      phase timed                  candidates
     gram_split   Gram tiles + reduction       0 (heuristic), 1, 2, 4, 8, 16, 32
     eloc_grid    local-energy recurrence      0 (one per item), 256, 512, 1024, 2048
-    sample_r     vector sampling recurrence   1, 4 (no effect on the matrix-core sampler)
+    sample_r     sampling recurrence          0 (built-in), 1, 4 (vector forms; no effect on FP32
+                                              chains of 64 or 128 units)
     jac_parts    Jacobian reverse pass        0 (built-in), 1, 2, 4
 """
 import json
@@ -24,7 +25,7 @@ from . import FORM_BF16_FP64
 CANDIDATES = {
     "gram_split": (0, 1, 2, 4, 8, 16, 32),
     "eloc_grid": (0, 256, 512, 1024, 2048),
-    "sample_r": (1, 4),
+    "sample_r": (0, 1, 4),
     "jac_parts": (0, 1, 2, 4),
 }
 PHASES = {

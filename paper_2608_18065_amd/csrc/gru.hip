@@ -10,6 +10,7 @@
 // (streamed from L2, reused across the R sequences) with the group's
 // previous hidden states (broadcast from LDS).  The output head is a
 // butterfly reduction over the H units of a group.
+#include "cell.hpp"
 #include "model.hpp"
 #include <cmath>
 
@@ -18,14 +19,6 @@ namespace minsr {
 template <typename T> struct VecT;
 template <> struct VecT<float> { typedef float4 type; static constexpr int V = 4; };
 template <> struct VecT<double> { typedef double2 type; static constexpr int V = 2; };
-
-__device__ inline float d_exp(float x) { return expf(x); }
-__device__ inline double d_exp(double x) { return exp(x); }
-__device__ inline float d_tanh(float x) { return tanhf(x); }
-__device__ inline double d_tanh(double x) { return tanh(x); }
-__device__ inline float d_log1p(float x) { return log1pf(x); }
-__device__ inline double d_log1p(double x) { return log1p(x); }
-template <typename T> __device__ inline T d_sigmoid(T x) { return T(1) / (T(1) + d_exp(-x)); }
 
 // ------------------------------------------------------------------ init
 __global__ void k_init_theta(double* theta, long long Np, InitBlocks b, uint64_t seed) {
@@ -769,17 +762,42 @@ static int forward_t(minsr_model* m, const Work<T>& w, int mode, int Ns, const d
   return dispatch_dim<T, 1>(m, a, (unsigned)a.n_items, s);
 }
 
+// Whether the matrix-core recurrence (recur_mm.hpp) is the faster one for a
+// call of Ns sequences; both give the same bits.  A lane of it works through
+// four units per site where the vector kernel's takes one, so while the vector
+// kernel has a SIMD for every wave it is the quicker of the two in short
+// chains; from about 1.5 waves a SIMD (Ns d_h = 98304) its weight streams and
+// its issue bound it.  Evaluation, 24 sites (1D) or 5 x 5 (2D), us, matrix
+// cores against vector: 1D FP32 d_h = 64 Ns = 1024 68 / 59, 2048 69 / 98;
+// d_h = 128 Ns = 512 126 / 123, 1024 126 / 170, 4096 129 / 558; 1D FP64 d_h =
+// 16 Ns = 2048 59 / 54, 4096 61 / 61; d_h = 32 Ns = 64 67 / 66, 4096 71 / 107.
+// 2D site work is larger and the vector kernel's windows go through memory:
+// 2D FP32 d_h = 16 Ns = 64 61 / 62, d_h = 64 93 / 121, d_h = 128 Ns = 512 209 /
+// 205, 1024 209 / 279, 4096 212 / 1050; FP64 d_h = 16 Ns = 64 70 / 81, d_h = 64
+// Ns = 4096 139 / 550.
+static bool rec_pays(const minsr_model* m, int Ns) {
+  if (!(m->f64 ? rec_f64_fits(m) : rec_f32_fits(m))) return false;
+  const bool short_chain = m->dim == 1 ? (!m->f64 || m->H < 32) : (!m->f64 && m->H == 128);
+  return !short_chain || (long long)Ns * m->H >= (m->f64 ? 65536 : 98304);
+}
+
 int launch_forward(minsr_model* m, int mode, int Ns, const double* uniforms, uint64_t key,
                    uint64_t counter, uint8_t* sigma, double* logpsi, void* states,
                    int store_every, double* site, hipStream_t s, const uint64_t* counter_ptr,
                    void* gates, uint32_t* zero_word) {
   if (Ns == 0) return MINSR_OK;
-  // FP32 chains of 64 or 128 units sample on the matrix cores; evaluation
-  // keeps the vector recurrence, whose arithmetic the Jacobian's checkpoint
+  // FP32 chains of 64 or 128 units sample with split FP16 products; the
+  // evaluation's arithmetic is the one that the Jacobian's checkpoint
   // recomputation repeats exactly
   if (mode == MODE_SAMPLE && sample_mfma_supported(m))
     return launch_sample_mfma(m, Ns, uniforms, key, counter, counter_ptr, sigma, logpsi, states,
                               store_every, site, m->dim == 1 ? gates : nullptr, zero_word, s);
+  // an explicit sample_r asks for the vector recurrence
+  if (m->tune_sample_r == 0 && rec_pays(m, Ns)) {
+    const RecCall c = {Ns, uniforms, key, counter, counter_ptr, sigma, logpsi, states, store_every,
+                       site, gates, zero_word};
+    return m->f64 ? launch_rec_f64(m, mode, c, s) : launch_rec_f32(m, mode, c, s);
+  }
   if (m->f64)
     return forward_t<double>(m, m->wd, mode, Ns, uniforms, key, counter, counter_ptr, sigma,
                              logpsi, states, store_every, site, gates, s, zero_word);
@@ -867,6 +885,8 @@ static int eloc_t(minsr_model* m, const Work<T>& w, const minsr_hamiltonian* H, 
     int rc;
     if (!m->f64 && !m->force_vector && eloc_mfma_supported(m))
       rc = launch_eloc_mfma(m, H, Ns, sigma, states, site, M, s);
+    else if (m->f64 && rec_f64_fits(m) && (m->dim == 1 || M <= 1024))
+      rc = launch_rec_eloc_f64(m, H, Ns, sigma, states, site, M, s);
     else
       rc = dispatch_dim<T, 4>(m, a, grid, s);
     if (rc) return rc;

@@ -893,6 +893,15 @@ __global__ __launch_bounds__(1024) void k_eloc_items(int* count, int M, int* ite
   if (tid == 0) count[M] = start[M];
 }
 
+int launch_eloc_lists(minsr_model* m, int Ns, const uint8_t* sigma, int M, hipStream_t s) {
+  if (M > 1024) return fail(MINSR_E_UNSUPPORTED, "more than 1024 exchange terms");
+  k_eloc_compact<<<M, 1024, 0, s>>>(sigma, m->bonds, m->N, Ns, m->elist, m->ecount, m->contrib);
+  MINSR_CHECK_LAUNCH();
+  k_eloc_items<<<1, 1024, 0, s>>>(m->ecount, M, m->eitems);
+  MINSR_CHECK_LAUNCH();
+  return MINSR_OK;
+}
+
 bool eloc_mfma_supported(minsr_model* m) {
   return !m->f64 && (m->H == 32 || m->H == 64 || m->H == 128);
 }
@@ -913,11 +922,8 @@ int launch_eloc_mfma(minsr_model* m, const minsr_hamiltonian* H, int Ns, const u
   a.M = M;
   if (a.n_items == 0) return MINSR_OK;
   if (H->kind == MINSR_HAM_J1J2) {
-    if (M > 1024) return fail(MINSR_E_UNSUPPORTED, "more than 1024 exchange terms");
-    k_eloc_compact<<<M, 1024, 0, s>>>(sigma, m->bonds, m->N, Ns, m->elist, m->ecount, m->contrib);
-    MINSR_CHECK_LAUNCH();
-    k_eloc_items<<<1, 1024, 0, s>>>(m->ecount, M, m->eitems);
-    MINSR_CHECK_LAUNCH();
+    const int rc = launch_eloc_lists(m, Ns, sigma, M, s);
+    if (rc) return rc;
     a.list = m->elist; a.count = m->ecount; a.items = m->eitems;
   }
   if (m->dim == 1 && m->H <= 64) {

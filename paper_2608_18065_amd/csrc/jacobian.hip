@@ -16,6 +16,7 @@
 // at a time from its two predecessors and keeps the adjoints of the last
 // 2 Lx states in an LDS window (a state feeds its right/left neighbour
 // and the state one row up).
+#include "cell.hpp"
 #include "model.hpp"
 #include <cmath>
 #include <type_traits>
@@ -25,14 +26,6 @@ namespace minsr {
 template <typename T> struct VecJ;
 template <> struct VecJ<float> { typedef float4 type; static constexpr int V = 4; };
 template <> struct VecJ<double> { typedef double2 type; static constexpr int V = 2; };
-
-__device__ inline float j_exp(float x) { return expf(x); }
-__device__ inline double j_exp(double x) { return exp(x); }
-__device__ inline float j_tanh(float x) { return tanhf(x); }
-__device__ inline double j_tanh(double x) { return tanh(x); }
-__device__ inline float j_log1p(float x) { return log1pf(x); }
-__device__ inline double j_log1p(double x) { return log1p(x); }
-template <typename T> __device__ inline T j_sigmoid(T x) { return T(1) / (T(1) + j_exp(-x)); }
 
 template <typename T> struct JacArgs {
   Work<T> w;
@@ -333,10 +326,10 @@ __global__ __launch_bounds__((JShape<H, P, WL>::NT)) void k_jacobian(JacArgs<T> 
               }
             }
             const T hprev = tx[sg][kk][j];
-            u = j_sigmoid(au);
-            rr = j_sigmoid(ar);
+            u = d_sigmoid(au);
+            rr = d_sigmoid(ar);
             ag = agg;
-            ht = j_tanh(rr * ag + ai);
+            ht = d_tanh(rr * ag + ai);
             hn = ((T)1 - u) * hprev + u * ht;
           }
           T z0 = (T)0, z1 = (T)0, q0 = (T)0, q1 = (T)0;
@@ -363,8 +356,8 @@ __global__ __launch_bounds__((JShape<H, P, WL>::NT)) void k_jacobian(JacArgs<T> 
             const T zz0 = z0 + c0, zz1 = z1 + c1;
             const T mx = zz0 > zz1 ? zz0 : zz1;
             const T d = zz0 > zz1 ? zz1 - zz0 : zz0 - zz1;
-            const T lse = mx + j_log1p(j_exp(d));
-            T p0 = j_exp(zz0 - lse), p1 = j_exp(zz1 - lse);
+            const T lse = mx + d_log1p(d_exp(d));
+            T p0 = d_exp(zz0 - lse), p1 = d_exp(zz1 - lse);
             if (a.zero_mag) {
               if (nup >= N / 2) { p0 = 0; p1 = 1; }
               else if (ndn >= N / 2) { p0 = 1; p1 = 0; }
@@ -445,10 +438,10 @@ __global__ __launch_bounds__((JShape<H, P, WL>::NT)) void k_jacobian(JacArgs<T> 
               agg = fma(wgs[v], xs[v], agg);
             }
           }
-          u = j_sigmoid(au);
-          rr = j_sigmoid(ar);
+          u = d_sigmoid(au);
+          rr = d_sigmoid(ar);
           ag = agg;
-          ht = j_tanh(rr * ag + ai);
+          ht = d_tanh(rr * ag + ai);
           hprev = hin;
           hk = ((T)1 - u) * hprev + u * ht;
           // head of site k (its conditional depends on the counts of sigma_{<k})
@@ -469,8 +462,8 @@ __global__ __launch_bounds__((JShape<H, P, WL>::NT)) void k_jacobian(JacArgs<T> 
             const T zz0 = z0 + c0, zz1 = z1 + c1;
             const T mx = zz0 > zz1 ? zz0 : zz1;
             const T d = zz0 > zz1 ? zz1 - zz0 : zz0 - zz1;
-            const T lse = mx + j_log1p(j_exp(d));
-            T p0 = j_exp(zz0 - lse), p1 = j_exp(zz1 - lse);
+            const T lse = mx + d_log1p(d_exp(d));
+            T p0 = d_exp(zz0 - lse), p1 = d_exp(zz1 - lse);
             if (a.zero_mag) {
               if (cu >= N / 2) { p0 = 0; p1 = 1; }
               else if (cd >= N / 2) { p0 = 1; p1 = 0; }
@@ -487,8 +480,8 @@ __global__ __launch_bounds__((JShape<H, P, WL>::NT)) void k_jacobian(JacArgs<T> 
         if (seed == 0) {
           T hp0, hp1;
           if (hsite) {
-            hp0 = j_exp((T)(tape ? lsc0 : sit[4 * k]));
-            hp1 = j_exp((T)(tape ? lsc1 : sit[4 * k + 1]));
+            hp0 = d_exp((T)(tape ? lsc0 : sit[4 * k]));
+            hp1 = d_exp((T)(tape ? lsc1 : sit[4 * k + 1]));
           } else {
             hp0 = thead[sg][kt][0];
             hp1 = thead[sg][kt][1];

@@ -110,6 +110,31 @@ int launch_forward(minsr_model* m, int mode, int Ns, const double* uniforms, uin
                    int store_every, double* site, hipStream_t s,
                    const uint64_t* counter_ptr = nullptr, void* gates = nullptr,
                    uint32_t* zero_word = nullptr);
+// recur_f32.hip, recur_f64.hip: the same recurrence on the FP32 / FP64 matrix
+// cores, outputs equal to k_forward's bit for bit (mode 0: sample, 1: evaluate)
+struct RecCall {
+  int Ns;
+  const double* uniforms;
+  uint64_t key, counter;
+  const uint64_t* counter_ptr;
+  uint8_t* sigma;
+  double* logpsi;
+  void* states;
+  int store_every;
+  double* site;
+  void* gates;
+  uint32_t* zero_word;
+};
+bool rec_f32_fits(const minsr_model* m);
+bool rec_f64_fits(const minsr_model* m);
+int launch_rec_f32(minsr_model* m, int mode, const RecCall& c, hipStream_t s);
+int launch_rec_f64(minsr_model* m, int mode, const RecCall& c, hipStream_t s);
+int launch_rec_eloc_f64(minsr_model* m, const minsr_hamiltonian* H, int Ns, const uint8_t* sigma,
+                        const void* states, const double* site, int M, hipStream_t s);
+// gru_mfma.hip: per exchange term, the samples with a nonzero matrix element
+// (elist, ecount) and the table of items of 32 of them (eitems); zeroes the
+// other samples' contributions
+int launch_eloc_lists(minsr_model* m, int Ns, const uint8_t* sigma, int M, hipStream_t s);
 // which: 1 = off-diagonal terms (the recurrence), 2 = diagonal + sum, 3 = both
 int launch_eloc(minsr_model* m, const minsr_hamiltonian* H, int Ns, const uint8_t* sigma,
                 const double* logpsi, const void* states, const double* site, double* eloc,
