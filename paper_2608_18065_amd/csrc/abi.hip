@@ -87,7 +87,7 @@ static int ensure_pinv_ws(minsr_model* m, hipStream_t s) {
 }
 
 static void release(minsr_model* m) {
-  void* ptrs[] = {m->theta, m->work, m->nbr, m->subA, m->bonds, m->states, m->gates, m->jdp, m->jtape, m->site,
+  void* ptrs[] = {m->theta, m->work, m->nbr, m->subA, m->bonds, m->states, m->jadj ? nullptr : m->gates, m->jdp, m->jtape, m->site,
                   m->contrib,
                   m->elist, m->ecount, m->eitems, m->eloc_q,
                   m->diag, m->ring, m->sigma, m->logpsi, m->eloc, m->stats, m->O, m->R,
@@ -204,11 +204,29 @@ int minsr_create_model(const minsr_model_desc* d, minsr_model** out) {
   rc = rc ? rc : alloc((void**)&m->nbr, nbr.size() * sizeof(int));
   rc = rc ? rc : alloc((void**)&m->subA, subA.size());
   rc = rc ? rc : alloc((void**)&m->bonds, std::max<size_t>(bonds.size(), 2) * sizeof(int));
-  rc = rc ? rc : alloc(&m->states, S * Nz * Hz * sz);
+  if (m->f64 ? jac_mm_f64_fits(m) : jac_mm_f32_fits(m)) {
+    // the states' allocation also holds the tapes of the matrix-core Jacobian:
+    // at most 4 GiB of them, for a large max_Ns in chunks of samples (whole
+    // rounds of 16 rows on 256 compute units where it holds that many); without
+    // memory for them k_jacobian serves the model
+    const size_t ng = m->dim == 2 ? 5 : 4;
+    const size_t per = jac_mm_site_elems(m) * Nz * sz;
+    size_t c = std::max<size_t>(16, ((size_t)4 << 30) / per / 16 * 16);
+    if (c > 4096) c = c / 4096 * 4096;
+    c = std::min(c, S);
+    const size_t st = S * Nz * Hz * sz, g = c * Nz * ng * Hz * sz, hd = c * Nz * 4 * sz;
+    if (!rc && alloc(&m->states, st + g * (m->cplx ? 3 : 2) + hd) == MINSR_OK) {
+      char* p = (char*)m->states + st;
+      m->gates = p; m->jhead = p + g; m->jadj = p + g + hd;
+      m->gates_ns = (int)c;
+    }
+  }
+  if (!m->states) rc = rc ? rc : alloc(&m->states, S * Nz * Hz * sz);
   // the Jacobian of these models reads the sampler's gate values instead of
   // recomputing them (checkpoint stride 1)
   if (m->dim == 1 && !m->f64 && m->H <= 64) {
     rc = rc ? rc : alloc(&m->gates, S * Nz * 4 * Hz * sz);
+    m->gates_ns = d->max_Ns;
     if (m->H >= 32) rc = rc ? rc : alloc(&m->jdp, (m->cplx ? 2 : 1) * S * Nz * 3 * Hz * sz);
   }
   if (const size_t te = jac_mfma_tape_elems(m->dim, m->f64, m->H, m->N, m->cplx, S))
@@ -385,7 +403,7 @@ int minsr_jacobian(minsr_model* m, int Ns, const uint8_t* dev_sigma, int out_dty
     return launch_center(Ns, 1, m->L.Np, m->O, 1, dev_O, out_dtype, m->colpart,
                          centered ? dev_colmean : nullptr, m->L.Np, s);
   }
-  const int C = m->dim == 1 ? ckpt_every : 1;
+  const int C = m->dim == 1 && !jac_mm(m) ? ckpt_every : 1;
   void* tape = C == 1 ? m->gates : nullptr;
   double* site = m->site;   // the pass's per-site conditionals
   rc = launch_forward(m, 1, Ns, nullptr, 0, 0, const_cast<uint8_t*>(dev_sigma), m->logpsi,
@@ -451,8 +469,9 @@ static int step_stages(minsr_model* m, const minsr_hamiltonian* H, const minsr_s
     return fail(MINSR_E_UNSUPPORTED, "the pseudo-inverse solve runs in FP64 only");
   if (cfg->form == MINSR_FORM_FP64_REF && !m->f64)
     return fail(MINSR_E_INVALID_ARG, "the FP64 reference form needs an FP64 model");
-  const int C = m->dim == 1 ? cfg->ckpt_every : 1;
-  if (C < 1 || C > 16) return fail(MINSR_E_INVALID_ARG, "ckpt_every in [1, 16]");
+  if (m->dim == 1 && (cfg->ckpt_every < 1 || cfg->ckpt_every > 16))
+    return fail(MINSR_E_INVALID_ARG, "ckpt_every in [1, 16]");
+  const int C = m->dim == 1 && !jac_mm(m) ? cfg->ckpt_every : 1;
 
   const size_t Np = m->L.Np;
   const int nb = m->cplx ? 2 : 1;
@@ -596,8 +615,9 @@ int minsr_step_adaptive(minsr_model* m, const minsr_hamiltonian* H, const minsr_
     if (st->dev_counter) return fail(MINSR_E_UNSUPPORTED, "LM mode needs a host-side counter");
     if (!(ad->omega > 1.0)) return fail(MINSR_E_INVALID_ARG, "omega must be > 1");
   }
-  const int C = m->dim == 1 ? cfg->ckpt_every : 1;
-  if (C < 1 || C > 16) return fail(MINSR_E_INVALID_ARG, "ckpt_every in [1, 16]");
+  if (m->dim == 1 && (cfg->ckpt_every < 1 || cfg->ckpt_every > 16))
+    return fail(MINSR_E_INVALID_ARG, "ckpt_every in [1, 16]");
+  const int C = m->dim == 1 && !jac_mm(m) ? cfg->ckpt_every : 1;
 
   const size_t Np = m->L.Np;
   const int nb = m->cplx ? 2 : 1;
@@ -792,7 +812,7 @@ static int raw_rows(minsr_model* m, int Ns, const uint8_t* dev_sigma, hipStream_
                                    m->logpsi, s);
     return rc ? rc : launch_linear_jacobian(m, Ns, dev_sigma, (double*)m->O, s);
   }
-  void* tape = m->dim == 1 ? m->gates : nullptr;
+  void* tape = m->gates;
   int rc = launch_forward(m, 1, Ns, nullptr, 0, 0, const_cast<uint8_t*>(dev_sigma), m->logpsi,
                           m->states, 1, m->site, s, nullptr, tape);
   if (rc) return rc;

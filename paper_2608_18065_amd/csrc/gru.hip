@@ -238,7 +238,7 @@ template <typename T> struct FwdArgs {
   const uint8_t* sigma_in;   // modes 1, 2
   double* logpsi;            // modes 0, 1: [Ns][2]
   T* states;                 // modes 0, 1: optional [Ns][N][H]
-  T* gates;                  // modes 0, 1 (1D): optional [Ns][N][4][H] u, r, g, ht
+  T* gates;                  // modes 0, 1: optional [Ns][N][4][H] u, r, g, ht (2D: [5], h' last)
   int store_every;
   double* site;              // modes 0, 1: optional [Ns][N][4]
   // local energies (mode 2)
@@ -573,9 +573,10 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
         if (a.mode != MODE_ELOC && a.states && act[r] &&
             ((k + 1) % a.store_every == 0 || DIM == 2))
           a.states[((size_t)s * N + k) * H + j] = hn[r];
-        if (DIM == 1 && a.mode != MODE_ELOC && a.gates && act[r]) {
-          T* gk = a.gates + ((size_t)s * N + k) * 4 * H;
+        if (a.mode != MODE_ELOC && a.gates && act[r]) {
+          T* gk = a.gates + ((size_t)s * N + k) * (DIM == 1 ? 4 : 5) * H;
           gk[j] = gu[r]; gk[H + j] = gr[r]; gk[2 * H + j] = ag[r]; gk[3 * H + j] = gt[r];
+          if (DIM == 2) gk[4 * H + j] = hin_own[r];
         }
       }
       // output head: logits (and phase pre-activations) of every sequence
@@ -752,7 +753,7 @@ static int forward_t(minsr_model* m, const Work<T>& w, int mode, int Ns, const d
   if (mode == MODE_SAMPLE) a.sigma_out = sigma; else a.sigma_in = sigma;
   a.logpsi = logpsi;
   a.states = (T*)states; a.store_every = store_every; a.site = site;
-  a.gates = (m->dim == 1 && store_every == 1 && mode != MODE_ELOC) ? (T*)gates : nullptr;
+  a.gates = (store_every == 1 && Ns <= m->gates_ns) ? (T*)gates : nullptr;
   // few sequences per block by default: the site loop is latency-bound
   const int R = m->tune_sample_r == 4 ? 4 : 1;
   const int B = seqs_per_block(m->H, R);

@@ -786,6 +786,11 @@ int launch_jacobian(minsr_model* m, int Ns, const uint8_t* sigma, const void* st
   if (m->dim == 2 && 2 * m->d.Lx > 32) return fail(MINSR_E_UNSUPPORTED, "2D lattices need Lx <= 16");
   if (ckpt_every < 1 || ckpt_every > SEGMAX)
     return fail(MINSR_E_INVALID_ARG, "ckpt_every must be in [1, 16]");
+  const bool tape = gates && Ns <= m->gates_ns;
+  if (jac_mm(m))
+    return m->f64 ? launch_jac_mm_f64(m, Ns, sigma, states, O, tape, s)
+                  : launch_jac_mm_f32(m, Ns, sigma, states, O, tape, s);
+  if (!tape) gates = nullptr;
   if (m->f64) return jac_t<double>(m, m->wd, Ns, sigma, states, ckpt_every, O, gates, site, s);
   // d_h = 128 chains: sample-batched reverse pass on the matrix cores
   // (an explicit thread split selects the per-sample kernel below)

@@ -1,0 +1,75 @@
+// The 16 x 16 x 4 FP32 and FP64 matrix products as the recurrence and its
+// reverse pass use them, and the shared-memory layout of their operands.
+#pragma once
+
+#include "mfma16.hpp"
+#include "model.hpp"
+
+namespace minsr {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4r;
+typedef __attribute__((ext_vector_type(4))) double f64x4r;
+
+// Lane l of a product: A[l % 16][l / 16], B[l / 16][l % 16]; result element v
+// is unit 4 (l / 16) + v of the tile, column l % 16 (the FP64 result rows are
+// permuted to that by the order of the A rows).  Both instructions add their
+// four products in ascending k as a chain of fused multiply-adds (compared
+// with such chains over 5e4 random tiles each: all bits equal).
+template <typename T> struct MM;
+template <> struct MM<float> {
+  typedef f32x4r acc;
+  typedef float4 vec;                 // one shared-memory read
+  static constexpr int V = 4;         // its elements; also the weight packing's vector
+  __device__ static int row(int r) { return r; }   // unit of A row r
+  __device__ static acc mma(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct MM<double> {
+  typedef f64x4r acc;
+  typedef double2 vec;
+  static constexpr int V = 2;
+  // result row r lies in lane group r % 4, element r / 4
+  __device__ static int row(int r) { return 4 * (r & 3) + (r >> 2); }
+  __device__ static acc mma(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+};
+
+// four consecutive values as one (FP64: two) 16-byte accesses
+__device__ inline void load4(const float* p, float (&v)[4]) {
+  const float4 x = *reinterpret_cast<const float4*>(p);
+  v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+}
+__device__ inline void load4(const double* p, double (&v)[4]) {
+  const double2 x = *reinterpret_cast<const double2*>(p), y = *reinterpret_cast<const double2*>(p + 2);
+  v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
+}
+__device__ inline void store4(float* p, const float (&v)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ inline void store4(double* p, const double (&v)[4]) {
+  *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
+  *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
+}
+
+// workgroup barrier ordering shared memory only; a single wave needs a fence
+template <int NW> __device__ inline void mm_sync() {
+  if constexpr (NW == 1) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    mf16::lds_barrier();
+  }
+}
+
+// A state (or adjoint) vector of 16 sequences as a B operand in shared
+// memory: [unit % 4][sequence][unit / 4], rows padded so that the 16-byte
+// reads of a quarter wave and the writes fall on different banks
+template <typename T> constexpr int mm_pitch(int H) { return H / 4 + MM<T>::V; }
+template <typename T> constexpr size_t mm_slot(int H) { return (size_t)64 * mm_pitch<T>(H); }
+
+constexpr size_t MM_LDS = 160 * 1024;
+
+}  // namespace minsr

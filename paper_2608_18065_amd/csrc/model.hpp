@@ -29,7 +29,11 @@ struct minsr_model {
   // ---- workspace sized for d.max_Ns
   int max_terms = 0;        // off-diagonal terms per sample (upper bound)
   void* states = nullptr;   // [max_Ns][N][H] hidden states
-  void* gates = nullptr;    // [max_Ns][N][4][H] gate tape (FP32 1D models, d_h <= 64)
+  void* gates = nullptr;    // gate tape of gates_ns samples: [.][N][4][H] (1D: FP32 d_h <= 64, FP64),
+                            //   [.][N][5][H] (2D models of the matrix-core Jacobian)
+  int gates_ns = 0;         // max_Ns, or fewer where the Jacobian works in chunks
+  void* jhead = nullptr;    // matrix-core Jacobian: [gates_ns][N][4] output-head conditionals
+  void* jadj = nullptr;     //   and [seeds][gates_ns][N][4 or 5][H] gate adjoints
   void* jdp = nullptr;      // [seeds][max_Ns][N][3][H] gate adjoints of the Jacobian (same models)
   void* jtape = nullptr;    // FP32 1D d_h = 128: [seeds][max_Ns][N][4][H] gate adjoints, then
                             //   [seeds][max_Ns][N][2] head adjoints (matrix-core Jacobian)
@@ -159,6 +163,19 @@ size_t jac_mfma_tape_elems(int dim, int f64, int H, int N, int cplx, size_t max_
 bool jac_mfma_supported(const minsr_model* m, int C);
 int launch_jacobian_mfma(minsr_model* m, int Ns, const uint8_t* sigma, int C, void* O,
                          const double* site, hipStream_t s);
+// jac_f32.hip, jac_f64.hip: the Jacobian of 2D models and FP64 chains on the
+// matrix cores (workspace gates, jhead, jadj); have_tape: gates holds the tape
+// of these samples
+bool jac_mm_f32_fits(const minsr_model* m);
+bool jac_mm_f64_fits(const minsr_model* m);
+size_t jac_mm_site_elems(const minsr_model* m);
+int launch_jac_mm_f32(minsr_model* m, int Ns, const uint8_t* sigma, const void* states, void* O,
+                      bool have_tape, hipStream_t s);
+int launch_jac_mm_f64(minsr_model* m, int Ns, const uint8_t* sigma, const void* states, void* O,
+                      bool have_tape, hipStream_t s);
+// whether launch_jacobian takes it: every state is needed and the checkpoint
+// stride has no effect
+inline bool jac_mm(const minsr_model* m) { return m->jadj && m->tune_jac_parts == 0; }
 // linalg.hip
 // centred (colmean != null) or plain copy of O into R with row stride ldo
 // (ldo >= Np; columns Np..ldo-1 are written as zeros)

@@ -27,36 +27,11 @@
 #include <mutex>
 
 #include "cell.hpp"
-#include "mfma16.hpp"
-#include "model.hpp"
+#include "mm.hpp"
 
 namespace minsr {
 
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) float f32x4r;
-typedef __attribute__((ext_vector_type(4))) double f64x4r;
-
-template <typename T> struct MM;
-template <> struct MM<float> {
-  typedef f32x4r acc;
-  typedef float4 vec;                 // one shared-memory read
-  static constexpr int V = 4;         // its elements; also the weight packing's vector
-  __device__ static int row(int r) { return r; }   // unit of A row r
-  __device__ static acc mma(float a, float b, acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct MM<double> {
-  typedef f64x4r acc;
-  typedef double2 vec;
-  static constexpr int V = 2;
-  // result row r lies in lane group r % 4, element r / 4
-  __device__ static int row(int r) { return 4 * (r & 3) + (r >> 2); }
-  __device__ static acc mma(double a, double b, acc c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-};
 
 __device__ inline float xor16_sum(float v) { return mf16::sum_xor16(v); }
 __device__ inline float xor32_sum(float v) { return mf16::sum_xor32(v); }
@@ -89,9 +64,10 @@ template <typename T> struct RecArgs {
   uint32_t* zero_word;
   const uint8_t* sigma_in;
   uint8_t* sigma_out;
-  double* logpsi;          // [Ns][2]
+  double* logpsi;          // optional [Ns][2]
   T* states;               // optional [Ns][N][H]
-  T* gates;                // optional [Ns][N][4][H] (1D)
+  T* gates;                // optional tape: 1D [Ns][N][4][H] u, r, candidate pre-activation,
+                           // candidate; 2D [Ns][N][5][H], the cell input h' last
   double* site;            // optional [Ns][N][4]
   // local energies
   const T* states_in;
@@ -108,13 +84,10 @@ template <typename T> struct RecArgs {
 
 // bytes of shared memory of a workgroup
 template <typename T> struct RecShape {
-  static constexpr int PAD = MM<T>::V;
-  static __host__ __device__ constexpr int pitch(int H) { return H / 4 + PAD; }
-  static __host__ __device__ constexpr size_t slot(int H) { return (size_t)64 * pitch(H); }
   static __host__ __device__ constexpr int slots(int dim, int Lx) { return dim == 1 ? 2 : Lx + 1; }
   static size_t bytes(int H, int dim, int Lx, int N) {
     const int ds = dim == 1 ? 2 : 4;
-    const size_t t = (size_t)(3 * ds + 8) * H + slot(H) * slots(dim, Lx) +
+    const size_t t = (size_t)(3 * ds + 8) * H + mm_slot<T>(H) * slots(dim, Lx) +
                      (size_t)2 * (H / 16) * 64;
     return t * sizeof(T) + 16 * 4 * 8 + (size_t)16 * N + 64;
   }
@@ -127,8 +100,8 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
   using vec_t = typename M::vec;
   constexpr int NW = H / 16, NT = 64 * NW, KT = H / 4, V = M::V;
   constexpr int ds = DIM == 1 ? 2 : 4;
-  constexpr int PT = RecShape<T>::pitch(H);
-  constexpr size_t SLOT = RecShape<T>::slot(H);
+  constexpr int PT = mm_pitch<T>(H);
+  constexpr size_t SLOT = mm_slot<T>(H);
   extern __shared__ __align__(16) unsigned char rsm[];
   T* xc = reinterpret_cast<T*>(rsm);                 // [3][ds][H]
   T* bias = xc + 3 * ds * H;                         // [4][H]
@@ -144,15 +117,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
   const int n = l & 15, q = l >> 4;
   const int N = a.N, Lx = a.Lx;
   const int j0 = 16 * w + 4 * q;                     // this lane's units j0 .. j0 + 3
-  auto sync = [&]() {
-    if constexpr (NW == 1) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
-      mf16::lds_barrier();
-    }
-  };
+  auto sync = [&]() { mm_sync<NW>(); };
 
   // which term and samples (local energies), or the 16 samples of the block
   int f1 = -1, f2 = -1, term = 0;
@@ -220,23 +185,6 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
   auto put = [&](T* slot, const T (&v)[4]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) slot[(e * 16 + n) * PT + 4 * w + q] = v[e];
-  };
-  auto load4 = [&](const T* p, T (&v)[4]) {
-    if constexpr (V == 4) {
-      const float4 x = *reinterpret_cast<const float4*>(p);
-      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    } else {
-      const double2 x = *reinterpret_cast<const double2*>(p), y = *reinterpret_cast<const double2*>(p + 2);
-      v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
-    }
-  };
-  auto store4 = [&](T* p, const T (&v)[4]) {
-    if constexpr (V == 4) {
-      *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    } else {
-      *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
-      *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
-    }
   };
   const int kstart = k0 + 1;
   if constexpr (DIM == 1) {
@@ -507,9 +455,10 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
         const size_t row = (size_t)s * N + k;
         if (a.states && (DIM == 2 || (k + 1) % a.store_every == 0))
           store4(a.states + row * H + j0, hn);
-        if (DIM == 1 && a.gates) {
-          T* g = a.gates + row * 4 * H + j0;
+        if (a.gates) {
+          T* g = a.gates + row * (DIM == 1 ? 4 : 5) * H + j0;
           store4(g, gu); store4(g + H, gr); store4(g + 2 * H, ag); store4(g + 3 * H, gt);
+          if constexpr (DIM == 2) store4(g + 4 * H, hin);
         }
       }
     }
@@ -544,7 +493,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
     double* o = a.contrib + ((size_t)term * a.Ns + s) * 2;
     o[0] = mel * e * cos(dim_);
     o[1] = mel * e * sin(dim_);
-  } else {
+  } else if (a.logpsi) {
     a.logpsi[2 * s] = 0.5 * lp;
     a.logpsi[2 * s + 1] = ph + 3.14159265358979323846 * (double)nA;
   }
@@ -555,12 +504,11 @@ template <typename T>
 static size_t rec_smem(const minsr_model* m) {
   return RecShape<T>::bytes(m->H, m->dim, m->d.Lx, m->N);
 }
-constexpr size_t REC_LDS = 160 * 1024;
 
 template <typename T>
 static bool rec_fits(const minsr_model* m) {
   return !m->linear && m->H >= 16 && m->H <= (sizeof(T) == 4 ? 128 : 64) &&
-         rec_smem<T>(m) <= REC_LDS;
+         rec_smem<T>(m) <= MM_LDS;
 }
 
 template <typename T, int H, int DIM, int MODE>
@@ -570,7 +518,7 @@ static int rec_launch(const RecArgs<T>& a, unsigned grid, size_t smem, hipStream
   hipError_t attr = hipSuccess;
   std::call_once(once, [&] {
     attr = hipFuncSetAttribute((const void*)k_rec_mm<T, H, DIM, MODE>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)REC_LDS);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)MM_LDS);
   });
   MINSR_HIP(attr);
   k_rec_mm<T, H, DIM, MODE><<<grid, 4 * H, smem, s>>>(a);
@@ -618,7 +566,7 @@ static int rec_forward(minsr_model* m, const Work<T>& w, int mode, const RecCall
   a.zero_word = c.zero_word;
   a.sigma_in = c.sigma; a.sigma_out = c.sigma;
   a.logpsi = c.logpsi; a.states = (T*)c.states; a.store_every = c.store_every;
-  a.gates = m->dim == 1 && c.store_every == 1 ? (T*)c.gates : nullptr;
+  a.gates = c.store_every == 1 && c.Ns <= m->gates_ns ? (T*)c.gates : nullptr;
   a.site = c.site;
   const unsigned grid = (unsigned)((c.Ns + 15) / 16);
   return mode == 0 ? rec_dispatch<T, RM_SAMPLE>(m, a, grid, s)
