@@ -835,7 +835,8 @@ int minsr_param_gram(minsr_model* m, int Ns, const uint8_t* dev_sigma, double* d
   rc = launch_center(Ns, nb, Np, m->O, m->f64, m->R, rdt, m->colpart, m->colmean, padded_ld(Np),
                      s);
   if (rc) return rc;
-  return launch_param_gram(m->R, m->f64, nb * Ns, (int)Np, padded_ld(Np), dev_S, s);
+  return launch_param_gram(m->R, m->f64, nb * Ns, (int)Np, padded_ld(Np), dev_S, m->gpart,
+                           m->gpart_elems, s);
 }
 
 int minsr_gram(minsr_model* m, int Ns, const uint8_t* dev_sigma, int form, double* dev_T,

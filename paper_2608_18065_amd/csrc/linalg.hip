@@ -460,70 +460,172 @@ __global__ __launch_bounds__(256, 2) void k_gram_f32(const float* R, int n, size
       }
 }
 
-// Vector SYRK tile kernel for FP32 / FP64 inputs: 64 x 64 tile, 256
-// threads with 4 x 4 outputs each, K staged 16 at a time.
+// FP64 products on v_mfma_f64_16x16x4, one 64 x 64 tile over one K range a
+// workgroup, 32 x 32 of it a wave (lane l: A[l % 16][l / 16], B[l / 16][l % 16];
+// result element v in row l / 16 + 4 v).  Bound by the products (64 cycles
+// each); the K ranges fill the chip from few tiles.  us, with the vector
+// kernels that were here (4 x 4 outputs a thread, no more than eight K ranges
+// of 256, or none): Gram n = 64, 960 columns 11 (52), n = 502, 5764 columns 41
+// (153; 20 at 73 TFLOP/s), n = 1400, 13188 columns 452 (354); parameter-space
+// metric 484 columns, 2048 rows 20 (531).
 constexpr int VT_ = 64, VK = 16;
+typedef __attribute__((ext_vector_type(4))) double f64x4s;
 
-template <typename TI, typename TA>
-__global__ __launch_bounds__(256) void k_gram_vec(const TI* R, int n, size_t Np, size_t kchunk,
-                                                  TA* part) {
-  __shared__ TA As[VK][VT_ + 1];
-  __shared__ TA Bs[VK][VT_ + 1];
+__device__ __forceinline__ void f64_products(const double (&x)[2][4], const double (&y)[2][4],
+                                             f64x4s (&acc)[2][2]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][v], y[j][v], acc[i][j], 0, 0, 0);
+}
+__device__ __forceinline__ void f64_store_tile(double* out, const f64x4s (&acc)[2][2], int w,
+                                               int lane) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        out[(32 * (w >> 1) + 16 * i + (lane >> 4) + 4 * v) * VT_ + 32 * (w & 1) + 16 * j +
+            (lane & 15)] = acc[i][j][v];
+}
+
+// T = R R^T of the FP64 forms.  The operands' rows are K-contiguous, and a load
+// instruction costs about four cycles per cache line it touches: reading them
+// from L2 in the operand layout (16 half lines an instruction) took 2100
+// cycles per 16 products.  So blocks of 32 columns go through shared memory in
+// whole lines, two buffers, the next block requested before the current
+// block's products; lane group q takes columns 4 q .. 4 q + 3 of each 16, so
+// its operands are two 16-byte reads.
+constexpr int GKB = 32, GKP = GKB + 2;   // columns per block, row pitch
+
+__global__ __launch_bounds__(256, 2) void k_gram_f64(const double* R, int n, size_t ld, int K,
+                                                     int kchunk, double* part) {
+  __shared__ __align__(16) double sm[2][2][VT_][GKP];
   int ti, tj;
   pair_decode(blockIdx.x, ti, tj);
-  const int split = blockIdx.y;
-  const size_t k0 = (size_t)split * kchunk;
-  const size_t k1 = min(Np, k0 + kchunk);
-  const int tid = threadIdx.x;
-  const int tr = (tid / 16) * 4, tc = (tid % 16) * 4;
-  TA acc[4][4];
+  const int k0 = blockIdx.y * kchunk, k1 = min(K, k0 + kchunk);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cl = lane & 15, q = lane >> 4;
+  f64x4s acc[2][2];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = (TA)0;
-  const int arow0 = ti * VT_, brow0 = tj * VT_;
-  for (size_t kk = k0; kk < k1; kk += VK) {
-    TA va[VT_ * VK / 256], vb[VT_ * VK / 256];
-#pragma unroll
-    for (int i = 0; i < VT_ * VK / 256; ++i) {
-      const int e = tid + 256 * i, r = e / VK, q = e % VK;
-      const size_t col = kk + q;
-      const int ra = arow0 + r, rb = brow0 + r;
-      va[i] = (col < k1 && ra < n) ? (TA)R[(size_t)ra * Np + col] : (TA)0;
-      vb[i] = (col < k1 && rb < n) ? (TA)R[(size_t)rb * Np + col] : (TA)0;
-    }
-#pragma unroll
-    for (int i = 0; i < VT_ * VK / 256; ++i) {
-      const int e = tid + 256 * i, r = e / VK, q = e % VK;
-      As[q][r] = va[i];
-      Bs[q][r] = vb[i];
-    }
+    for (int j = 0; j < 2; ++j) acc[i][j] = f64x4s{0.0, 0.0, 0.0, 0.0};
+  // thread: 16 bytes at column 2 (tid % 16) of rows tid / 16 + 16 i of both
+  // operands (rows past n repeat the last; the reduction drops their results)
+  const int lr = tid >> 4, lc = 2 * (tid & 15);
+  // (named values: an array of loaded values ends up in scratch memory here)
+  auto row = [&](int t, int i) { return R + (size_t)min(t * VT_ + lr + 16 * i, n - 1) * ld + lc; };
+  const double *a0 = row(ti, 0), *a1 = row(ti, 1), *a2 = row(ti, 2), *a3 = row(ti, 3);
+  const double *b0 = row(tj, 0), *b1 = row(tj, 1), *b2 = row(tj, 2), *b3 = row(tj, 3);
+  double2 va0, va1, va2, va3, vb0, vb1, vb2, vb3;
+#define MINSR_GRAM_LOAD(k)                                                        \
+  do {                                                                            \
+    const unsigned kk_ = (unsigned)min((k), K - GKB);                             \
+    va0 = *reinterpret_cast<const double2*>(a0 + kk_);                            \
+    va1 = *reinterpret_cast<const double2*>(a1 + kk_);                            \
+    va2 = *reinterpret_cast<const double2*>(a2 + kk_);                            \
+    va3 = *reinterpret_cast<const double2*>(a3 + kk_);                            \
+    vb0 = *reinterpret_cast<const double2*>(b0 + kk_);                            \
+    vb1 = *reinterpret_cast<const double2*>(b1 + kk_);                            \
+    vb2 = *reinterpret_cast<const double2*>(b2 + kk_);                            \
+    vb3 = *reinterpret_cast<const double2*>(b3 + kk_);                            \
+  } while (0)
+  auto put = [&](int b, int o, int i, double2 v) {
+    *reinterpret_cast<double2*>(&sm[b][o][lr + 16 * i][lc]) = v;
+  };
+#define MINSR_GRAM_STORE(b)                                                       \
+  do {                                                                            \
+    put(b, 0, 0, va0); put(b, 0, 1, va1); put(b, 0, 2, va2); put(b, 0, 3, va3);   \
+    put(b, 1, 0, vb0); put(b, 1, 1, vb1); put(b, 1, 2, vb2); put(b, 1, 3, vb3);   \
+  } while (0)
+  if (k0 < k1) {
+    MINSR_GRAM_LOAD(k0);
+    MINSR_GRAM_STORE(0);
     __syncthreads();
+    int b = 0;
+    for (int k = k0; k < k1; k += GKB) {
+      MINSR_GRAM_LOAD(k + GKB);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < VK; ++q) {
-      TA av[4], bv[4];
+      for (int h = 0; h < GKB; h += VK) {
+        double x[2][4], y[2][4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = As[q][tr + a];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = Bs[q][tc + b];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = fma(av[a], bv[b], acc[a][b]);
+        for (int i = 0; i < 2; ++i) {
+          const double* px = &sm[b][0][32 * (w >> 1) + 16 * i + cl][h + 4 * q];
+          const double* py = &sm[b][1][32 * (w & 1) + 16 * i + cl][h + 4 * q];
+          const double2 x0 = *reinterpret_cast<const double2*>(px), x1 = *reinterpret_cast<const double2*>(px + 2);
+          const double2 y0 = *reinterpret_cast<const double2*>(py), y1 = *reinterpret_cast<const double2*>(py + 2);
+          x[i][0] = x0.x; x[i][1] = x0.y; x[i][2] = x1.x; x[i][3] = x1.y;
+          y[i][0] = y0.x; y[i][1] = y0.y; y[i][2] = y1.x; y[i][3] = y1.y;
+        }
+        f64_products(x, y, acc);
+      }
+      MINSR_GRAM_STORE(b ^ 1);
+      b ^= 1;
+      __syncthreads();
     }
-    __syncthreads();
   }
-  TA* out = part + ((size_t)split * gridDim.x + blockIdx.x) * VT_ * VT_;
+#undef MINSR_GRAM_LOAD
+#undef MINSR_GRAM_STORE
+  f64_store_tile(part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * VT_ * VT_, acc, w, lane);
+}
+
+// S = R^T R (the parameter-space metric): an operand load is 16 columns of four
+// rows, whole lines, so the operands come straight from L2; two buffers of 16
+// rows, the next one requested without a condition (clamped at the end), so
+// the wait before a buffer's products leaves the other's loads in flight
+template <typename TR>
+__global__ __launch_bounds__(256, 2) void k_param_gram(const TR* R, size_t ld, int rows,
+                                                       int kchunk, double* part, int pair0) {
+  int ti, tj;
+  pair_decode(pair0 + blockIdx.x, ti, tj);
+  const int k0 = blockIdx.y * kchunk, k1 = min(rows, k0 + kchunk);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cl = lane & 15, q = lane >> 4;
+  const TR* pr = R + ti * VT_ + 32 * (w >> 1) + cl;
+  const TR* pc = R + tj * VT_ + 32 * (w & 1) + cl;
+  f64x4s acc[2][2];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) out[(tr + a) * VT_ + tc + b] = acc[a][b];
+    for (int j = 0; j < 2; ++j) acc[i][j] = f64x4s{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](int k, double (&x)[2][4], double (&y)[2][4]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int kk = k + 4 * v + q;
+      const size_t at = (size_t)min(kk, rows - 1) * ld;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const TR xv = pr[at + 16 * i];
+        x[i][v] = kk < k1 ? (double)xv : 0.0;
+        y[i][v] = (double)pc[at + 16 * i];
+      }
+    }
+  };
+  if (k0 < k1) {
+    double xa[2][4], ya[2][4], xb[2][4], yb[2][4];
+    load(k0, xa, ya);
+    for (int k = k0; k < k1; k += 2 * VK) {
+      load(k + VK, xb, yb);
+      f64_products(xa, ya, acc);
+      load(k + 2 * VK, xa, ya);
+      f64_products(xb, yb, acc);
+    }
+  }
+  f64_store_tile(part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * VT_ * VT_, acc, w, lane);
 }
 
 // sum the split-K partials in split order; write T (lower and mirror)
 template <typename TA, typename TT>
 __device__ __forceinline__ void gram_reduce_tile(const TA* part, int npairs, int nsplit,
-                                                 int tile, int n, TT* T, int pair, int sub) {
+                                                 int tile, int n, TT* T, int pair, int sub,
+                                                 int pair0 = 0) {
   // one 32 x 32 sub-tile per workgroup: partials summed in split order, the
   // tile written row-wise and its mirror through a shared-memory transpose,
   // so both stores are coalesced rows
@@ -532,7 +634,7 @@ __device__ __forceinline__ void gram_reduce_tile(const TA* part, int npairs, int
   const int sr = sub / nsub, sc = sub % nsub;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   int ti, tj;
-  pair_decode(pair, ti, tj);
+  pair_decode(pair0 + pair, ti, tj);
   // partials summed in split order, eight splits' loads in flight
   TA s[4] = {(TA)0, (TA)0, (TA)0, (TA)0};
   for (int k0 = 0; k0 < nsplit; k0 += 8) {
@@ -569,8 +671,8 @@ __device__ __forceinline__ void gram_reduce_tile(const TA* part, int npairs, int
 
 template <typename TA, typename TT>
 __global__ __launch_bounds__(256) void k_gram_reduce(const TA* part, int npairs, int nsplit,
-                                                     int tile, int n, TT* T) {
-  gram_reduce_tile<TA, TT>(part, npairs, nsplit, tile, n, T, blockIdx.y, blockIdx.x);
+                                                     int tile, int n, TT* T, int pair0 = 0) {
+  gram_reduce_tile<TA, TT>(part, npairs, nsplit, tile, n, T, blockIdx.y, blockIdx.x, pair0);
 }
 
 __global__ __launch_bounds__(256) void k_gram_reduce_grouped(const GramJob* jobs, int njobs) {
@@ -585,15 +687,29 @@ __global__ __launch_bounds__(256) void k_gram_reduce_grouped(const GramJob* jobs
 
 constexpr int MAX_SPLIT = 64;
 
-// split-K factor: requested, else enough for ~1024 workgroups; at most
-// MAX_SPLIT, 4096 workgroups in total, and chunks of >= 256 columns
-static int pick_split(int npairs, size_t Np, int want) {
+// split-K factor: requested, else enough to fill the chip; at most
+// MAX_SPLIT, 4096 workgroups in total, and chunks of >= 256 columns (FP64: 64)
+static int pick_split(int npairs, size_t Np, int want, bool f64) {
   // default: about 4096 workgroups, at most 8 partial tiles per pair
   int S = want > 0 ? want : std::min(8, (4096 + npairs - 1) / npairs);
   const int by_grid = std::max(1, (4096 + npairs - 1) / npairs);
-  int maxS = (int)std::max<size_t>(1, std::min<size_t>(MAX_SPLIT, Np / 256));
+  int maxS = (int)std::max<size_t>(1, std::min<size_t>(MAX_SPLIT, Np / (f64 ? 64 : 256)));
   maxS = std::min(maxS, by_grid);
   return std::max(1, std::min(S, maxS));
+}
+
+// FP64 tiles, two workgroups a compute unit: the split that minimises rounds
+// of 512 workgroups times the K range of one, with a little for the partial
+// tiles (n = 1400, 253 pairs: 2 ranges 458 us, 3 578; n = 502, 36 pairs: 14
+// ranges 41 us, 8 52)
+static int f64_split(int npairs, size_t K) {
+  int best = 1;
+  double cost = 1e300;
+  for (int q = 1; q <= MAX_SPLIT && (q == 1 || K / q >= 64); ++q) {
+    const double c = (double)(((long long)npairs * q + 511) / 512) / q + 0.002 * q;
+    if (c < cost) { cost = c; best = q; }
+  }
+  return best;
 }
 
 // workspace for the largest split any setting may request
@@ -601,7 +717,8 @@ size_t gram_partial_bytes(int n, size_t Np, int dtype) {
   const int tile = dtype == MINSR_F64 ? VT_ : GT;
   const int nt = (n + tile - 1) / tile;
   const int npairs = nt * (nt + 1) / 2;
-  const int S = std::max(pick_split(npairs, Np, 0), pick_split(npairs, Np, MAX_SPLIT));
+  const bool f64 = dtype == MINSR_F64;
+  const int S = std::max(pick_split(npairs, Np, 0, f64), pick_split(npairs, Np, MAX_SPLIT, f64));
   const size_t el = dtype == MINSR_F32 ? 4 : 8;
   return (size_t)S * npairs * tile * tile * el;
 }
@@ -629,8 +746,9 @@ static void gram_plan(int npairs, size_t Np, size_t ld, int dtype, int want_spli
       if (cost < best * (1.0 - 1e-9)) { best = cost; want = q; }
     }
   }
-  S = pick_split(npairs, Np, want);
-  const size_t kgran = dtype == MINSR_BF16 ? 64 : dtype == MINSR_F32 ? FK : VK;
+  if (dtype == MINSR_F64 && want_split <= 0) want = f64_split(npairs, Np);
+  S = pick_split(npairs, Np, want, dtype == MINSR_F64);
+  const size_t kgran = dtype == MINSR_F32 ? FK : 64;
   kchunk = (ld + S - 1) / S;
   kchunk = (kchunk + kgran - 1) / kgran * kgran;
 }
@@ -695,12 +813,40 @@ int launch_gram(int n, size_t Np, const void* R, int dtype, double* T, float* gp
   } else {
     double* dp = reinterpret_cast<double*>(gpart);
     if (which & 1) {
-      k_gram_vec<double, double><<<grid, 256, 0, s>>>((const double*)R, n, ld, kchunk, dp);
+      k_gram_f64<<<grid, 256, 0, s>>>((const double*)R, n, ld, (int)ld, (int)kchunk, dp);
       MINSR_CHECK_LAUNCH();
     }
     if (which & 2) k_gram_reduce<double, double><<<rgrid, 256, 0, s>>>(dp, npairs, S, tile, n, T);
   }
   MINSR_CHECK_LAUNCH();
+  return MINSR_OK;
+}
+
+// S = R^T R over `rows` rows of R (row stride ld, zero columns past Np), exactly
+// symmetric: tiles over the lower triangle, each split over the rows as far as
+// the partial-tile workspace holds, then reduced and mirrored as the Gram's
+int launch_param_gram(const void* R, int r_f64, int rows, int Np, size_t ld, double* S,
+                      float* gpart, size_t gpart_elems, hipStream_t s) {
+  if (Np <= 0) return MINSR_OK;
+  const int nt = (Np + VT_ - 1) / VT_, npairs = nt * (nt + 1) / 2;
+  const size_t tile_bytes = (size_t)VT_ * VT_ * 8, room = gpart_elems * sizeof(float);
+  double* part = reinterpret_cast<double*>(gpart);
+  size_t split = (size_t)f64_split(npairs, (size_t)rows);
+  split = std::min(split, room / (tile_bytes * npairs));
+  // too many tiles for one pass of the workspace: runs of tiles, one K range
+  const int run = split >= 1 ? npairs : (int)std::max<size_t>(1, room / tile_bytes);
+  if (split < 1) split = 1;
+  int kchunk = (rows + (int)split - 1) / (int)split;
+  kchunk = (kchunk + 2 * VK - 1) / (2 * VK) * 2 * VK;
+  for (int p0 = 0; p0 < npairs; p0 += run) {
+    const int np = std::min(run, npairs - p0);
+    const dim3 grid((unsigned)np, (unsigned)split);
+    if (r_f64) k_param_gram<double><<<grid, 256, 0, s>>>((const double*)R, ld, rows, kchunk, part, p0);
+    else k_param_gram<float><<<grid, 256, 0, s>>>((const float*)R, ld, rows, kchunk, part, p0);
+    MINSR_CHECK_LAUNCH();
+    k_gram_reduce<double, double><<<dim3(4, (unsigned)np), 256, 0, s>>>(part, np, (int)split, VT_, Np, S, p0);
+    MINSR_CHECK_LAUNCH();
+  }
   return MINSR_OK;
 }
 
