@@ -37,18 +37,6 @@ size_t packed_elems(minsr_model* m);
 void bind_work(minsr_model* m);
 size_t gram_partial_bytes(int n, size_t Np, int dtype);
 
-template <typename TO>
-__global__ void k_vjp(const TO* O, int Ns, int two, size_t Np, const double* g, double scale,
-                      double* out) {
-  size_t col = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= Np) return;
-  double s = 0.0;
-  for (int r = 0; r < Ns; ++r) s += g[2 * r] * (double)O[(size_t)r * Np + col];
-  if (two)
-    for (int r = 0; r < Ns; ++r) s += g[2 * r + 1] * (double)O[((size_t)Ns + r) * Np + col];
-  out[col] = s * scale;
-}
-
 __global__ void k_widen(const float* a, size_t n, double* out) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = (double)a[i];
@@ -436,13 +424,8 @@ int minsr_logpsi_vjp(minsr_model* m, int Ns, const uint8_t* dev_sigma, const dou
   rc = launch_jacobian(m, Ns, dev_sigma, m->states, 1, m->O, nullptr, nullptr, s, m->gates,
                        m->site);
   if (rc) return rc;
-  const size_t Np = m->L.Np;
-  const double scale = std::sqrt((double)Ns);
-  const unsigned grid = (unsigned)((Np + 255) / 256);
-  if (m->f64) k_vjp<double><<<grid, 256, 0, s>>>((const double*)m->O, Ns, m->cplx, Np, dev_g, scale, dev_grad_theta);
-  else k_vjp<float><<<grid, 256, 0, s>>>((const float*)m->O, Ns, m->cplx, Np, dev_g, scale, dev_grad_theta);
-  MINSR_CHECK_LAUNCH();
-  return MINSR_OK;
+  return launch_vjp(Ns, m->cplx ? 2 : 1, m->L.Np, m->O, m->f64, dev_g, std::sqrt((double)Ns),
+                    m->colpart, dev_grad_theta, s);
 }
 
 // the step in three stages (bits of `stages`): 1 = sampling through the

@@ -182,6 +182,10 @@ inline bool jac_mm(const minsr_model* m) { return m->jadj && m->tune_jac_parts =
 int launch_center(int rows_per_block, int nblocks, size_t Np, const void* O, int in_f64,
                   void* R, int out_dtype, double* colpart, double* colmean, size_t ldo,
                   hipStream_t s, void* Rlo = nullptr);
+// out[k] = scale * sum over the blocks b and rows s of g[2 s + b] O[b rows_per_block + s][k]
+// (FP64 sums; part: as launch_center's colpart)
+int launch_vjp(int rows_per_block, int nblocks, size_t Np, const void* O, int in_f64,
+               const double* g, double scale, double* part, double* out, hipStream_t s);
 // the step keeps O' with rows padded to a multiple of 64 columns
 inline size_t padded_ld(size_t Np) { return (Np + 63) / 64 * 64; }
 // one instance's Gram in a grouped launch (BF16 split form): its work items
