@@ -954,13 +954,10 @@ int launch_eloc_mfma(minsr_model* m, const minsr_hamiltonian* H, int Ns, const u
   }
   const unsigned nt = 64u * (unsigned)(m->H / 32);
 #define MINSR_ELOC_MFMA(HH, DD) k_eloc_mfma<HH, DD><<<grid, nt, 0, s>>>(a)
-  if (m->dim == 1) {
-    MINSR_ELOC_MFMA(128, 1);
-  } else {
-    if (m->H == 32) MINSR_ELOC_MFMA(32, 2);
-    else if (m->H == 64) MINSR_ELOC_MFMA(64, 2);
-    else MINSR_ELOC_MFMA(128, 2);
-  }
+  // 2D comes here only where the window of states does not fit shared memory
+  if (m->H != 128) return fail(MINSR_E_UNSUPPORTED, "more than 1024 exchange terms");
+  if (m->dim == 1) MINSR_ELOC_MFMA(128, 1);
+  else MINSR_ELOC_MFMA(128, 2);
 #undef MINSR_ELOC_MFMA
   MINSR_CHECK_LAUNCH();
   return MINSR_OK;

@@ -135,6 +135,8 @@ int launch_rec_f32(minsr_model* m, int mode, const RecCall& c, hipStream_t s);
 int launch_rec_f64(minsr_model* m, int mode, const RecCall& c, hipStream_t s);
 int launch_rec_eloc_f64(minsr_model* m, const minsr_hamiltonian* H, int Ns, const uint8_t* sigma,
                         const void* states, const double* site, int M, hipStream_t s);
+int launch_rec_eloc_f32(minsr_model* m, const minsr_hamiltonian* H, int Ns, const uint8_t* sigma,
+                        const void* states, const double* site, int M, hipStream_t s);
 // gru_mfma.hip: per exchange term, the samples with a nonzero matrix element
 // (elist, ecount) and the table of items of 32 of them (eitems); zeroes the
 // other samples' contributions
