@@ -433,8 +433,46 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
     }
     __syncthreads();
 
+    // log-conditionals and phases from the head sums, nu and nd of the
+    // earlier spins being 0 and 1
+    auto conditional = [&](T z0, T z1, T q0, T q1, int nu, int nd, T& lp0, T& lp1, T& ph0, T& ph1) {
+      const T zz0 = z0 + c0, zz1 = z1 + c1;
+      const T mx = zz0 > zz1 ? zz0 : zz1;
+      const T d = zz0 > zz1 ? zz1 - zz0 : zz0 - zz1;   // -|z0 - z1|
+      const T lse = mx + d_log1p(d_exp(d));
+      lp0 = zz0 - lse;
+      lp1 = zz1 - lse;
+      if (a.zero_mag) {
+        const int half = N / 2;
+        if (nu >= half) { lp0 = -INFINITY; lp1 = (T)0; }
+        else if (nd >= half) { lp0 = (T)0; lp1 = -INFINITY; }
+      }
+      ph0 = ph1 = (T)0;
+      if (a.cplx) {
+        const T aa0 = q0 + cp0, aa1 = q1 + cp1;
+        ph0 = PI * aa0 / ((T)1 + fabs(aa0));
+        ph1 = PI * aa1 / ((T)1 + fabs(aa1));
+      }
+    };
+    // evaluation, one sequence per group: conditionals and spins are handled
+    // GB sites at a time (the load of the next spin and the conditional lay in
+    // every site's chain: 40 sites, d_h = 16 Ns = 33 48 -> 37 us, d_h = 64 Ns =
+    // 256 75 -> 61, FP64 d_h = 16 Ns = 256 91 -> 65)
+    constexpr int GB = H < 64 ? H : 64;
+    const bool defer = R == 1 && a.mode == MODE_EVAL;
+    uint64_t smask = 0;                  // the batch's spins, bit i of site kb + i
+    T keep[4] = {(T)0, (T)0, (T)0, (T)0};
+
     for (int k = kstart; k < N; ++k) {
       const int cb = k & 1, nb = cb ^ 1;
+      if constexpr (R == 1) {
+        if (defer && k % GB == 0) {
+          const int li = tid & (GB - 1);
+          const int sp = k + li < N ? a.sigma_in[(size_t)sidx[0] * N + k + li] & 1 : 0;
+          smask = __ballot(sp) >> ((tid & 63) - li);
+          if constexpr (GB < 64) smask &= (1ull << GB) - 1;
+        }
+      }
       T hin_own[R];
       int kh = -1, kv = -1;
       int sh[R], sv[R];
@@ -624,25 +662,48 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
         __syncthreads();   // red is rewritten at the next site
       }
       // conditional, sampling decision and accumulation
+      if constexpr (R == 1) {
+        if (defer) {
+          // evaluation: the spin is known and nothing later waits for the
+          // conditional, so lane k % GB of the group keeps the site's head
+          // sums and the group forms GB conditionals at once
+          const int li = tid & (GB - 1), at = k % GB;
+          if (li == at) { keep[0] = z0[0]; keep[1] = z1[0]; keep[2] = q0[0]; keep[3] = q1[0]; }
+          sprev[0] = (int)(smask >> at) & 1;
+          if (at == GB - 1 || k == N - 1) {
+            const int kb = k - at, ks = kb + li, cnt = at + 1;
+            const bool on = li < cnt;
+            const int v = (int)(smask >> li) & 1;
+            const uint64_t valid = cnt >= 64 ? ~0ull : (1ull << cnt) - 1;
+            const int before = __popcll(~smask & valid & ((1ull << li) - 1));
+            T lp0, lp1, ph0, ph1;
+            conditional(keep[0], keep[1], keep[2], keep[3], nup[0] + before, kb + li - nup[0] - before,
+                        lp0, lp1, ph0, ph1);
+            const double lpv = (double)(v == 0 ? lp0 : lp1), phv = (double)(v == 0 ? ph0 : ph1);
+            const int base = (tid & 63) - li;
+            for (int i = 0; i < cnt; ++i) {         // in site order
+              lp[0] += __shfl(lpv, base + i, 64);
+              if (a.cplx) ph[0] += __shfl(phv, base + i, 64);
+            }
+            if (a.site && on && j < GB && act[0]) {
+              double* st = a.site + ((size_t)sidx[0] * N + ks) * 4;
+              st[0] = (double)lp0; st[1] = (double)lp1; st[2] = (double)ph0; st[3] = (double)ph1;
+            }
+            if (a.marshall) {
+              const uint64_t b = __ballot(on && v && a.subA[min(ks, N - 1)]);
+              nA[0] += __popcll((b >> base) & valid);
+            }
+            nup[0] += __popcll(~smask & valid);
+            smask = 0;
+          }
+        }
+      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
+        if (R == 1 && defer) continue;
         const int s = sidx[r];
-        const T zz0 = z0[r] + c0, zz1 = z1[r] + c1;
-        const T mx = zz0 > zz1 ? zz0 : zz1;
-        const T d = zz0 > zz1 ? zz1 - zz0 : zz0 - zz1;   // -|z0 - z1|
-        const T lse = mx + d_log1p(d_exp(d));
-        T lp0 = zz0 - lse, lp1 = zz1 - lse;
-        if (a.zero_mag) {
-          const int half = N / 2;
-          if (nup[r] >= half) { lp0 = -INFINITY; lp1 = (T)0; }
-          else if (ndn[r] >= half) { lp0 = (T)0; lp1 = -INFINITY; }
-        }
-        T ph0 = (T)0, ph1 = (T)0;
-        if (a.cplx) {
-          const T aa0 = q0[r] + cp0, aa1 = q1[r] + cp1;
-          ph0 = PI * aa0 / ((T)1 + fabs(aa0));
-          ph1 = PI * aa1 / ((T)1 + fabs(aa1));
-        }
+        T lp0, lp1, ph0, ph1;
+        conditional(z0[r], z1[r], q0[r], q1[r], nup[r], ndn[r], lp0, lp1, ph0, ph1);
         int v;
         if (a.mode == MODE_SAMPLE) {
           double u;
@@ -767,19 +828,23 @@ static int forward_t(minsr_model* m, const Work<T>& w, int mode, int Ns, const d
 // call of Ns sequences; both give the same bits.  A lane of it works through
 // four units per site where the vector kernel's takes one, so while the vector
 // kernel has a SIMD for every wave it is the quicker of the two in short
-// chains; from about 1.5 waves a SIMD (Ns d_h = 98304) its weight streams and
-// its issue bound it.  Evaluation, 24 sites (1D) or 5 x 5 (2D), us, matrix
-// cores against vector: 1D FP32 d_h = 64 Ns = 1024 68 / 59, 2048 69 / 98;
-// d_h = 128 Ns = 512 126 / 123, 1024 126 / 170, 4096 129 / 558; 1D FP64 d_h =
-// 16 Ns = 2048 59 / 54, 4096 61 / 61; d_h = 32 Ns = 64 67 / 66, 4096 71 / 107.
+// chains; from about 1.5 waves a SIMD (Ns d_h = 98304; evaluation of narrow
+// chains, whose vector sites are shortest, twice that) its weight streams and
+// its issue bound it.  24 sites (1D) or 5 x 5 (2D), us, matrix cores / vector:
+// 1D FP32 sampling d_h = 32 Ns = 2048 63 / 57, 4096 64 / 69; evaluation d_h = 32
+// Ns = 4096 52 / 48, 8192 65 / 76, d_h = 64 Ns = 1024 61 / 51, 1536 61 / 82, d_h
+// = 128 Ns = 512 120 / 115, 768 120 / 160, 4096 124 / 573; 1D FP64 sampling d_h
+// = 16 Ns = 2048 65 / 64, 4096 67 / 71, d_h = 32 Ns = 64 74 / 72, 4096 81 / 119.
 // 2D site work is larger and the vector kernel's windows go through memory:
-// 2D FP32 d_h = 16 Ns = 64 61 / 62, d_h = 64 93 / 121, d_h = 128 Ns = 512 209 /
-// 205, 1024 209 / 279, 4096 212 / 1050; FP64 d_h = 16 Ns = 64 70 / 81, d_h = 64
-// Ns = 4096 139 / 550.
-static bool rec_pays(const minsr_model* m, int Ns) {
+// 2D FP32 sampling d_h = 16 Ns = 64 63 / 74, d_h = 128 Ns = 512 223 / 210, 768
+// 222 / 283, 4096 228 / 1062; FP64 d_h = 16 Ns = 64 75 / 91, d_h = 64 Ns = 4096
+// 153 / 559.
+static bool rec_pays(const minsr_model* m, int mode, int Ns) {
   if (!(m->f64 ? rec_f64_fits(m) : rec_f32_fits(m))) return false;
   const bool short_chain = m->dim == 1 ? (!m->f64 || m->H < 32) : (!m->f64 && m->H == 128);
-  return !short_chain || (long long)Ns * m->H >= (m->f64 ? 65536 : 98304);
+  if (!short_chain) return true;
+  const bool narrow = mode == MODE_EVAL && m->dim == 1 && m->H <= 32;
+  return (long long)Ns * m->H >= (m->f64 ? 65536 : 98304) * (narrow ? 2 : 1);
 }
 
 int launch_forward(minsr_model* m, int mode, int Ns, const double* uniforms, uint64_t key,
@@ -794,7 +859,7 @@ int launch_forward(minsr_model* m, int mode, int Ns, const double* uniforms, uin
     return launch_sample_mfma(m, Ns, uniforms, key, counter, counter_ptr, sigma, logpsi, states,
                               store_every, site, m->dim == 1 ? gates : nullptr, zero_word, s);
   // an explicit sample_r asks for the vector recurrence
-  if (m->tune_sample_r == 0 && rec_pays(m, Ns)) {
+  if (m->tune_sample_r == 0 && rec_pays(m, mode, Ns)) {
     const RecCall c = {Ns, uniforms, key, counter, counter_ptr, sigma, logpsi, states, store_every,
                        site, gates, zero_word};
     return m->f64 ? launch_rec_f64(m, mode, c, s) : launch_rec_f32(m, mode, c, s);
