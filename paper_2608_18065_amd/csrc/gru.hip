@@ -296,7 +296,9 @@ template <int H> struct GroupReduce {
   }
 };
 
-template <typename T, int H, int DIM, int R>
+// EVAL: mode 1 with one sequence per group (conditionals and spins handled in
+// batches, below)
+template <typename T, int H, int DIM, int R, bool EVAL = false>
 __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
   using VT = typename VecT<T>::type;
   constexpr int V = VecT<T>::V;
@@ -318,9 +320,9 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
   const VT* fw = reinterpret_cast<const VT*>(w.fw);
   const VT* f2 = reinterpret_cast<const VT*>(w.f2);
   const int ds = DIM == 1 ? 2 : 4;
-  // FP32 1D, d_h <= 64: the thread's gate weights (3 H values of its unit)
-  // stay in registers for the whole kernel, so a site costs no weight loads
-  constexpr bool WR = sizeof(T) == 4 && DIM == 1 && H <= 64 && R == 1;
+  // 1D, d_h <= 64 (FP64: 16): the thread's gate weights (3 H values of its
+  // unit) stay in registers for the whole kernel, so a site costs no weight loads
+  constexpr bool WR = DIM == 1 && H <= (sizeof(T) == 4 ? 64 : 16) && R == 1;
   VT wreg[WR ? (H / V) * 3 : 1];
   if constexpr (WR) {
 #pragma unroll
@@ -459,13 +461,21 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
     // every site's chain: 40 sites, d_h = 16 Ns = 33 48 -> 37 us, d_h = 64 Ns =
     // 256 75 -> 61, FP64 d_h = 16 Ns = 256 91 -> 65)
     constexpr int GB = H < 64 ? H : 64;
-    const bool defer = R == 1 && a.mode == MODE_EVAL;
+    // (d_h = 128 decides at run time: its separate instantiation schedules the
+    // weight loads worse, 40 sites Ns = 33 158 -> 218 us)
+    constexpr bool can_defer = EVAL || (R == 1 && H == 128 && DIM == 1);
+    const bool defer = EVAL || (can_defer && a.mode == MODE_EVAL);
     uint64_t smask = 0;                  // the batch's spins, bit i of site kb + i
     T keep[4] = {(T)0, (T)0, (T)0, (T)0};
 
     for (int k = kstart; k < N; ++k) {
       const int cb = k & 1, nb = cb ^ 1;
-      if constexpr (R == 1) {
+      // sampling, one sequence per group of fewer than 64 lanes: lane c draws
+      // Philox block c of the next 4 GB sites
+      if constexpr (R == 1 && H < 64 && !EVAL)
+        if (a.mode == MODE_SAMPLE && !a.uniforms && k % (4 * GB) == 0)
+          rpre = philox4x64_10(ctr, (uint64_t)sidx[0], (uint64_t)((k >> 2) + (tid & (GB - 1))), 0, a.key, 0);
+      if constexpr (can_defer) {
         if (defer && k % GB == 0) {
           const int li = tid & (GB - 1);
           const int sp = k + li < N ? a.sigma_in[(size_t)sidx[0] * N + k + li] & 1 : 0;
@@ -583,6 +593,7 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
         for (int k4 = 0; k4 < H / V; ++k4)
           gate_step(k4, wreg[k4 * 3 + 0], wreg[k4 * 3 + 1], wreg[k4 * 3 + 2]);
       } else {
+        // (24 loads in flight instead of six: d_h = 128 evaluation 158 -> 215 us)
 #pragma unroll 2
         for (int k4 = 0; k4 < H / V; ++k4)
           gate_step(k4, fw[(k4 * H + j) * 3 + 0], fw[(k4 * H + j) * 3 + 1],
@@ -662,7 +673,7 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
         __syncthreads();   // red is rewritten at the next site
       }
       // conditional, sampling decision and accumulation
-      if constexpr (R == 1) {
+      if constexpr (can_defer) {
         if (defer) {
           // evaluation: the spin is known and nothing later waits for the
           // conditional, so lane k % GB of the group keeps the site's head
@@ -700,7 +711,8 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if (R == 1 && defer) continue;
+        if constexpr (can_defer)
+          if (defer) continue;
         const int s = sidx[r];
         T lp0, lp1, ph0, ph1;
         conditional(z0[r], z1[r], q0[r], q1[r], nup[r], ndn[r], lp0, lp1, ph0, ph1);
@@ -715,6 +727,10 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
             const int lo = __builtin_amdgcn_readlane((int)(uint32_t)wq, k >> 2);
             const int hi = __builtin_amdgcn_readlane((int)(uint32_t)(wq >> 32), k >> 2);
             u = u01(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+          } else if constexpr (R == 1 && H < 64) {
+            const int q = k & 3;
+            const uint64_t wq = q == 0 ? rpre.w[0] : q == 1 ? rpre.w[1] : q == 2 ? rpre.w[2] : rpre.w[3];
+            u = u01(__shfl((unsigned long long)wq, (tid & 63) - (tid & (GB - 1)) + (k % (4 * GB) >> 2), 64));
           } else {
             if ((k & 3) == 0)
               rw[r] = philox4x64_10(ctr, (uint64_t)s, (uint64_t)(k >> 2), 0, a.key, 0);
@@ -765,7 +781,9 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
 
 template <typename T, int H, int DIM, int R>
 static int launch_fwd_t(const FwdArgs<T>& a, unsigned grid, hipStream_t s) {
-  k_forward<T, H, DIM, R><<<grid, 256, 0, s>>>(a);
+  if (R == 1 && H <= 64 && a.mode == MODE_EVAL)
+    k_forward<T, H, DIM, R, R == 1 && H <= 64><<<grid, 256, 0, s>>>(a);
+  else k_forward<T, H, DIM, R><<<grid, 256, 0, s>>>(a);
   MINSR_CHECK_LAUNCH();
   return MINSR_OK;
 }

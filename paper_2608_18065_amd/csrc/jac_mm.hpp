@@ -55,15 +55,17 @@ template <typename T> struct JmArgs {
 };
 
 // ------------------------------------------------------------ output head
-// one wave per 64 (sample, site) pairs: per pair the sums over the units as
+// one wave per PW (sample, site) pairs: per pair the sums over the units as
 // k_jacobian forms them (an xor butterfly over 64 lanes, then the two
-// wavefronts' halves at d_h = 128), then lane i the conditional of pair i
-template <typename T, int H>
+// wavefronts' halves at d_h = 128), then lane i the conditional of pair i.
+// PW is 64, or 16 where that leaves SIMDs idle (640 pairs, d_h = 16: 12.9 ->
+// 6 us)
+template <typename T, int H, int PW>
 __global__ __launch_bounds__(256) void k_jac_head(JmArgs<T> a) {
   constexpr int W = H < 64 ? H : 64, G = H / W;
   constexpr int PP = 64 / W;              // pairs side by side in a wave
   const int lane = threadIdx.x & 63;
-  const long long p0 = 64 * (4ll * blockIdx.x + (threadIdx.x >> 6));
+  const long long p0 = PW * (4ll * blockIdx.x + (threadIdx.x >> 6));
   const long long np = (long long)a.ns * a.N;
   if (p0 >= np) return;                   // uniform per wave
   const int j = lane % W, sub = lane / W;
@@ -75,7 +77,7 @@ __global__ __launch_bounds__(256) void k_jac_head(JmArgs<T> a) {
     for (int c = 0; c < 4; ++c) u[g][c] = c < nq ? a.w.head[c * H + g * W + j] : (T)0;
   const T* st = a.states + (size_t)a.s_base * a.N * H;
   T z[4] = {(T)0, (T)0, (T)0, (T)0};
-  for (int i0 = 0; i0 < 64; i0 += PP) {
+  for (int i0 = 0; i0 < PW; i0 += PP) {
     const long long p = min(p0 + i0 + sub, np - 1);
     T h[G];
 #pragma unroll
@@ -100,7 +102,7 @@ __global__ __launch_bounds__(256) void k_jac_head(JmArgs<T> a) {
     }
   }
   const long long p = p0 + lane;
-  if (p >= np) return;
+  if (lane >= PW || p >= np) return;
   const int N = a.N, k = (int)(p % N);
   const long long sl = p / N;
   const T zz0 = z[0] + a.w.headb[0], zz1 = z[1] + a.w.headb[1];
@@ -558,7 +560,8 @@ static int jm_chunk(const JmArgs<T>& a, hipStream_t s) {
   MINSR_HIP(attr);
   const unsigned seeds = a.cplx ? 2 : 1;
   const long long pairs = (long long)a.ns * a.N;
-  k_jac_head<T, H><<<(unsigned)((pairs + 255) / 256), 256, 0, s>>>(a);
+  if (pairs > 65536) k_jac_head<T, H, 64><<<(unsigned)((pairs + 255) / 256), 256, 0, s>>>(a);
+  else k_jac_head<T, H, 16><<<(unsigned)((pairs + 63) / 64), 256, 0, s>>>(a);
   MINSR_CHECK_LAUNCH();
   k_jac_rev<T, H, DIM, P><<<seeds * (unsigned)((a.ns + 15) / 16), 4 * H,
                             jm_rev_smem<T, H, P>(DIM, a.Lx), s>>>(a);

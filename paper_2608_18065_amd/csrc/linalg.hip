@@ -2139,8 +2139,16 @@ __global__ void k_update_part<double>(const double* R, int n, size_t Np, size_t 
   size_t col = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (col >= Np) return;
   const int r0 = blockIdx.y * RC, r1 = min(n, r0 + RC);
+  // eight rows' loads in flight, summed in order (n = 64, 962 columns 13.7 -> 8.8 us)
   double s = 0.0;
-  for (int r = r0; r < r1; ++r) s += R[(size_t)r * ld + col] * x[r];
+  for (int r = r0; r < r1; r += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = R[(size_t)min(r + u, r1 - 1) * ld + col];   // tail rows repeat, unused
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (r + u < r1) s += v[u] * x[r + u];
+  }
   part[(size_t)blockIdx.y * Np + col] = s;
 }
 
