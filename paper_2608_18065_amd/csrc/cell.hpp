@@ -15,16 +15,22 @@ __device__ inline float d_sigmoid(float x) { return 1.f / (1.f + d_exp(-x)); }
 // library's functions (IEEE division, special cases, tanh in extended
 // precision: about 400 instructions a unit) the FP64 kernels are bound by
 // their issue.  The ones below reduce x = k ln 2 + r, |r| <= ln 2 / 2 (ln 2 in
-// two parts, by fma), take the Taylor polynomial of e^r - 1 to r^13 (remainder
-// below 5e-18), and divide by Newton's iteration on the hardware reciprocal:
-// about 110 instructions a unit.  Mean and largest error in units in the last
-// place over 4e6 arguments against 80-bit values, in brackets the library's:
-// exp 0.263, 1.01 (0.256, 0.88); logistic 0.380, 2.38 (0.381, 2.38); tanh
-// 0.183, 1.89 (0.161, 0.86); log1p 0.286, 2.12 (0.204, 0.63).  log psi, local
-// energies and steps against 64-bit torch keep their errors (10-site FP64
-// step: direction 1.8e-14, 2.0e-14 with the library's).  NaN arguments give
-// NaN.
-__device__ inline double expm1_poly(double r) {
+// two parts, the first of 32 bits so that k times it is exact; r carries its
+// rounding error c), take the Taylor polynomial of e^r - 1 to r^13 (remainder
+// below 5e-18), and divide by Newton's iteration on the hardware reciprocal,
+// the leading sums and quotients with their rounding errors carried: about
+// 130 instructions a unit.  Mean and largest error in units in the last place
+// over 4e6 arguments against 80-bit values, in brackets the library's: exp
+// 0.250, 0.64 (0.256, 0.88); logistic 0.378, 2.38 (0.381, 2.38); tanh 0.160,
+// 0.86 (0.161, 0.86); log1p 0.204, 0.71 (0.204, 0.63).  NaN arguments give NaN.
+
+// e^r - 1 = r + t, x = k ln 2 + r; t holds r's rounding error too
+__device__ inline void exp_parts(double x, double& k, double& r, double& t) {
+  k = rint(x * 1.4426950408889634074);
+  const double x1 = fma(-k, 0x1.62e42feep-1, x);       // exact
+  const double l2 = 1.9082149292705877e-10;             // the rest of ln 2
+  r = fma(-k, l2, x1);
+  const double c = fma(-k, l2, x1 - r);
   double p = 1.0 / 6227020800.0;
   p = fma(p, r, 1.0 / 479001600.0);
   p = fma(p, r, 1.0 / 39916800.0);
@@ -36,13 +42,7 @@ __device__ inline double expm1_poly(double r) {
   p = fma(p, r, 1.0 / 120.0);
   p = fma(p, r, 1.0 / 24.0);
   p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  return fma(p * r, r, r);
-}
-// x = k ln 2 + r
-__device__ inline double reduce_ln2(double x, double& k) {
-  k = rint(x * 1.4426950408889634074);
-  return fma(-k, 2.3190468138462995584e-17, fma(-k, 0.69314718055994530942, x));
+  t = fma(0.5 * r, r, fma(r * r, r * p, c));
 }
 // 1 / d for 2^-1000 < |d| < 2^1000
 __device__ inline double rcp_newton(double d) {
@@ -50,41 +50,42 @@ __device__ inline double rcp_newton(double d) {
   y = fma(fma(-d, y, 1.0), y, y);
   return fma(fma(-d, y, 1.0), y, y);
 }
-// a / (c + b) for c >= |b|: the sum's rounding error goes into the remainder
-__device__ inline double quotient(double a, double c, double b) {
-  const double d = c + b, dl = b - (d - c);
-  const double y = rcp_newton(d), q = a * y;
-  return fma(fma(-q, dl, fma(-d, q, a)), y, q);
+// e^x for -746 <= x <= 711 (beyond these the result is 0 or infinite)
+__device__ inline double exp_clamped(double x) {
+  double k, r, t;
+  exp_parts(x, k, r, t);
+  const double s = 1.0 + r, lo = r - (s - 1.0);
+  return ldexp(s + (lo + t), (int)k);
 }
 __device__ inline double d_exp(double x) {
-  double k;
-  // beyond these the result is 0 or infinite
-  const double r = reduce_ln2(fmax(fmin(x, 711.0), -746.0), k);
-  const double e = ldexp(1.0 + expm1_poly(r), (int)k);
+  const double e = exp_clamped(fmax(fmin(x, 711.0), -746.0));
   return x != x ? x : e;
 }
 __device__ inline double d_tanh(double x) {
-  double k;
-  const double r = reduce_ln2(fmin(2.0 * fabs(x), 44.0), k);   // tanh(22) rounds to 1
-  const double s = ldexp(1.0, (int)k);
-  const double e = fma(s, expm1_poly(r), s - 1.0);              // e^2|x| - 1
-  const double t = copysign(e > 2.0 ? quotient(e, e, 2.0) : quotient(e, 2.0, e), x);
-  return x != x ? x : t;
+  double k, r, t;
+  exp_parts(fmin(2.0 * fabs(x), 44.0), k, r, t);                // tanh(22) rounds to 1
+  // e^2|x| - 1 = h + l
+  const double s = ldexp(1.0, (int)k), a = s - 1.0, b = fma(s, r, a);
+  const double v = fma(s, t, fma(s, r, a - b));
+  const double h = b + v, l = v - (h - b);
+  // (h + l) / (h + l + 2)
+  const double c = fmax(h, 2.0), d = h + 2.0, dl = (fmin(h, 2.0) - (d - c)) + l;
+  const double y = rcp_newton(d), q = h * y;
+  const double z = copysign(fma(fma(-q, d, h) + fma(-q, dl, l), y, q), x);
+  return x != x ? x : z;
 }
 __device__ inline double d_sigmoid(double x) {
-  double k;
-  const double r = reduce_ln2(fmax(fmin(-x, 708.0), -746.0), k);
-  const double e = ldexp(1.0 + expm1_poly(r), (int)k);
-  const double t = rcp_newton(1.0 + e);
+  const double t = rcp_newton(1.0 + exp_clamped(fmax(fmin(-x, 708.0), -746.0)));
   return x != x ? x : t;
 }
-// log(1 + e) for 0 <= e <= 1: 2 atanh(s) with s = f / (2 + f), where 1 + f is
-// 1 + e, or (1 + e) / 2 above sqrt(2) - 1, so |s| <= 0.172 and the series to
-// s^23 is complete to 1e-19
+// log(1 + e) for 0 <= e <= 1: with 1 + f = 1 + e, or (1 + e) / 2 from e = 1/2
+// (both exact), and s = f / (2 + f), |s| <= 0.2, log(1 + f) = 2 atanh(s) =
+// f - (f^2 / 2 - s (f^2 / 2 + p)), p = 2 s^2 / 3 + 2 s^4 / 5 + ...; the series
+// to s^22 is complete to 1e-18
 __device__ inline double d_log1p(double e) {
-  const bool big = e > 0.41421356237309504880;
+  const bool big = e >= 0.5;
   const double f = big ? 0.5 * (e - 1.0) : e;
-  const double s = quotient(f, 2.0, f), z = s * s;
+  const double s = f * rcp_newton(2.0 + f), z = s * s;
   double p = 2.0 / 23.0;
   p = fma(p, z, 2.0 / 21.0);
   p = fma(p, z, 2.0 / 19.0);
@@ -96,8 +97,11 @@ __device__ inline double d_log1p(double e) {
   p = fma(p, z, 2.0 / 7.0);
   p = fma(p, z, 2.0 / 5.0);
   p = fma(p, z, 2.0 / 3.0);
-  p = fma(p * z, s, s + s);
-  return big ? 0.69314718055994530942 + p : p;
+  const double g = 0.5 * f;
+  const double l2 = big ? 0.69314718055994530942 : 0.0, l2l = big ? 2.3190468138462995584e-17 : 0.0;
+  const double a = l2 + f, al = f - (a - l2);
+  const double b = fma(-g, f, a), bl = fma(-g, f, a - b);
+  return b + fma(s, fma(p, z, g * f), bl + (al + l2l));
 }
 
 }  // namespace minsr
