@@ -22,16 +22,16 @@
 
 namespace minsr {
 
-// panel width of the tridiagonalisation: the single-workgroup column
-// kernel's dot products with the panel grow with it, the number of
-// trailing rank-2 TNB updates with its inverse (8 beat 16 at n = 4096)
-constexpr int TNB = 8;
+// panel width of the tridiagonalisation: the panel vectors that a column
+// reads grow with it (k_tri_row 3.9 us at position 0, 4.1 in the second
+// half), the number of trailing rank-2 TNB updates (22 us) with its inverse
+constexpr int TNB = 16;
 constexpr int PINV_MAX_N = 4096;
 
 // ------------------------------------------------------------ workspace
 struct PinvWs {
   // tridiagonalisation
-  double *A, *V, *W, *tau, *d, *e, *bq, *g, *s12, *scal, *pc, *pd;
+  double *A, *V, *W, *tau, *d, *e, *bq, *y, *s12, *scal, *col, *pd;
   // divide and conquer, per depth parity (ping-pong)
   double *ev[2], *fr[2], *lr[2], *cv[2], *tv[2];
   // per-merge scratch, indexed by position in [0, n)
@@ -76,8 +76,8 @@ static PinvWs carve(double* base, int n, int nmax) {
   auto take = [&](size_t k) { double* r = p; p += k; return r; };
   w.A = take(N * N);
   w.V = take(TNB * N); w.W = take(TNB * N);
-  w.tau = take(N); w.d = take(N); w.e = take(N); w.bq = take(N); w.g = take(N);
-  w.s12 = take(2 * TNB); w.scal = take(8); w.pc = take(N); w.pd = take(N);
+  w.tau = take(N); w.d = take(N); w.e = take(N); w.bq = take(N); w.y = take(N);
+  w.s12 = take(2 * TNB); w.scal = take(8); w.col = take(N); w.pd = take(N);
   for (int i = 0; i < 2; ++i) { w.ev[i] = take(N); w.fr[i] = take(N); w.lr[i] = take(N);
                                 w.cv[i] = take(N); w.tv[i] = take(N); }
   w.es = take(N); w.dl = take(N); w.wv = take(N); w.dlo = take(N); w.taus = take(N);
@@ -140,227 +140,176 @@ __device__ __host__ inline void node_of(int n, int lev, int slot, int& lo, int& 
 }
 
 // ================================================== tridiagonalisation
+// Two launches a column.  Every launch waits for the one before it, so a
+// column's time is two launches, their loads' latencies and the stream of the
+// trailing matrix through k_tri_mv; both kernels therefore run on as many
+// workgroups as there are rows for, form the scalars redundantly from
+// partial sums, and request every operand before the first wait.  (With the
+// reflector, the panel's dot products and w on one workgroup the two kernels
+// took 9.7 + 10.8 us on average at n = 4096; now 4.0 + 11.2,
+// and 22 instead of 2 x 19 us for the update of 16 columns.)
 struct TriArgs {
-  double *A, *V, *W, *tau, *d, *e, *bq, *g, *s12, *pc, *pd;
+  double *A, *V, *W, *tau, *d, *e, *bq, *y, *s12, *col, *pd, *pn, *pb, *scal;
   int n;
 };
 
 constexpr int TBS = 1024;
-constexpr int TPT = PINV_MAX_N / TBS;      // rows per thread in single-workgroup kernels
+constexpr int TMR = 8;                     // rows (wavefronts) of a k_tri_mv workgroup
 
-// Column j at position p of its panel, one workgroup.  With the product
-// g = (A - V W^T - W V^T) v_{j-1} and its partial dots g.v from the previous
-// column's multi-workgroup kernel, w_{j-1} = tau g + alpha v with
-// alpha = -tau^2/2 g.v is finalised elementwise; column j (whose panel terms
-// up to q = p - 2 the same kernel subtracted) receives the q = p - 1 term;
-// then the reflector, b <- H b, and s1 = W^T v, s2 = V^T v over q < p.
-__global__ __launch_bounds__(TBS) void k_tri_col(TriArgs a, int j, int p, int npd) {
-  __shared__ double red[TBS / 64];
-  __shared__ double sh[4];
-  __shared__ double vsh[PINV_MAX_N], wsh[PINV_MAX_N], vlsh[PINV_MAX_N];
-  __shared__ double gpart[32];
-  const int n = a.n, tid = threadIdx.x;
-  double col[TPT], wl[TPT], vl[TPT];
-  // every global operand of this thread's rows is requested up front, so
-  // the kernel waits for memory once rather than once per phase
-  double gl_[TPT], pc_[TPT], bq_[TPT];
-  const double* vprev = a.V + (size_t)(p > 0 ? p - 1 : 0) * n;
+// value of lane q (a constant) in every lane
+__device__ __forceinline__ double lane_value(double v, int q) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, q);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), q);
+  return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+
+// Rows i > j, one per thread, after column j's product y = A v (panel position
+// p): g = y - sum_{q<p} V_q s1[q] + W_q s2[q], w = tau g + alpha v with alpha =
+// -tau^2 / 2 g.v and g.v = y.v - 2 s1.s2; the right-hand side's reflection;
+// then column j + 1 of the updated matrix, A[j+1][i] - sum_{q<=p} V_q[i]
+// W_q[j+1] + W_q[i] V_q[j+1], and this workgroup's parts of its norm and of its
+// product with the right-hand side, rows j + 3 onwards.  p < 0: column 0 as it
+// is.  Q is p rounded up.
+template <int Q>
+__global__ __launch_bounds__(64) void k_tri_row(TriArgs a, int j, int p, int npd) {
+  const int n = a.n, lane = threadIdx.x;
+  const int i = j + 1 + 64 * blockIdx.x + lane, ii = min(i, n - 1);
+  double vq[Q ? Q : 1], wq[Q ? Q : 1];
 #pragma unroll
-  for (int u = 0; u < TPT; ++u) {
-    const int i = j + tid + TBS * u;
-    const bool ok = i < n;
-    vl[u] = (ok && p > 0) ? vprev[i] : 0.0;
-    gl_[u] = (ok && p > 0) ? a.g[i] : 0.0;
-    pc_[u] = ok ? (p > 0 ? a.pc[i] : a.A[(size_t)j * n + i]) : 0.0;
-    bq_[u] = ok ? a.bq[i] : 0.0;
+  for (int q = 0; q < Q; ++q) {
+    const size_t o = (size_t)(q < p ? q : 0) * n + ii;
+    vq[q] = a.V[o];
+    wq[q] = a.W[o];
   }
-  if (p > 0) {
-    const double tp = a.tau[j - 1];
+  const double aj = a.A[(size_t)(j + 1) * n + ii], b0 = a.bq[ii];
+  double w = 0.0, vi = 0.0, Wj = 0.0, vb = 0.0, col = aj;
+  if (p >= 0) {
+    const int lq = lane < p ? lane : 0;
+    double l1 = a.s12[lq], l2 = a.s12[TNB + lq];
+    double lv = a.V[(size_t)lq * n + j + 1], lw = a.W[(size_t)lq * n + j + 1];
+    const double yi = a.y[ii], yj = a.y[j + 1], tp = a.tau[j];
+    vi = a.V[(size_t)p * n + ii];
+    vb = a.scal[1];
     double sp = 0.0;
-    for (int k = tid; k < npd; k += TBS) sp += a.pd[k];
-    const double alpha = -0.5 * tp * tp * block_sum(sp, red);
 #pragma unroll
-    for (int u = 0; u < TPT; ++u) {
-      const int i = j + tid + TBS * u;
-      wl[u] = 0.0;
-      if (i < n) {
-        wl[u] = tp * gl_[u] + alpha * vl[u];
-        a.W[(size_t)(p - 1) * n + i] = wl[u];
-      }
+    for (int k = 0; k < PINV_MAX_N / TMR / 64; ++k) {
+      const double x = a.pd[min(lane + 64 * k, npd - 1)];
+      sp += lane + 64 * k < npd ? x : 0.0;
     }
-    if (tid == 0) { sh[1] = wl[0]; sh[2] = vl[0]; }      // row j
-    __syncthreads();
-    const double Wj = sh[1], Vj = sh[2];
+    if (lane >= p) l1 = l2 = lv = lw = 0.0;
+    const double alpha = -0.5 * tp * tp * wave_sum(sp - 2.0 * (l1 * l2));
+    Wj = tp * (yj - wave_sum(lv * l1 + lw * l2)) + alpha;       // v[j+1] = 1
+    double g = 0.0, c = 0.0;
 #pragma unroll
-    for (int u = 0; u < TPT; ++u) {
-      const int i = j + tid + TBS * u;
-      col[u] = i < n ? pc_[u] - (vl[u] * Wj + wl[u] * Vj) : 0.0;
+    for (int q = 0; q < Q; ++q) {
+      const double v_ = q < p ? vq[q] : 0.0, w_ = q < p ? wq[q] : 0.0;
+      g = fma(w_, lane_value(l2, q), fma(v_, lane_value(l1, q), g));
+      c = fma(w_, lane_value(lv, q), fma(v_, lane_value(lw, q), c));
     }
-  } else {
-#pragma unroll
-    for (int u = 0; u < TPT; ++u) { col[u] = pc_[u]; wl[u] = 0.0; }
+    w = tp * (yi - g) + alpha * vi;
+    col = (aj - c) - (vi * Wj + w);
   }
-  if (tid == 0) a.d[j] = col[0];
-  if (j == n - 1) return;
-  // reflector for x = col[j+1 ..]: alpha = x_0, sigma^2 = |x_1..|^2
-  if (tid == 1) sh[0] = col[0];          // row j + 1 is owned by thread 1
-  double ps = 0.0;
-#pragma unroll
-  for (int u = 0; u < TPT; ++u) {
-    const int i = j + tid + TBS * u;
-    if (i >= j + 2 && i < n) ps += col[u] * col[u];
+  const double b = b0 - vb * vi;
+  if (i < n) {
+    if (p >= 0) a.W[(size_t)p * n + i] = w;
+    a.col[i] = col;
+    a.bq[i] = b;
+    if (i == j + 1) a.d[i] = col;
   }
-  const double sig2 = block_sum(ps, red);   // its barriers publish sh[0]
-  const double alpha = sh[0];
+  const double x = i >= j + 3 && i < n ? col : 0.0;
+  const double pn = wave_sum(x * x), pb = wave_sum(x * b);
+  if (lane == 0) { a.pn[blockIdx.x] = pn; a.pb[blockIdx.x] = pb; }
+}
+
+// The reflector of column j (position p of its panel) from col, formed by
+// every workgroup: v = col sc with v[j+1] = 1, in LDS.  Then one wavefront a
+// row: y[i] = A[i] . v for i > j; and, as 2p more rows, s1[q] = W_q . v and
+// s2[q] = V_q . v.  nrow workgroups take A's rows, workgroup b rows 8 (rb + b)
+// onwards with rb a multiple of 8: a row stays on the same XCD from column to
+// column, so that trailing matrices within the L2 caches stay there.
+__global__ __launch_bounds__(64 * TMR) void k_tri_mv(TriArgs a, int j, int p, int rb, int nrow,
+                                                     int npn) {
+  __shared__ double vs[PINV_MAX_N];
+  __shared__ double pdw[TMR];
+  const int n = a.n, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int len = n - j - 1, blk = blockIdx.x;
+  const bool tail = blk >= nrow;
+  const int i = TMR * (rb + blk) + wv;                     // row of A
+  const int q = TMR * (blk - nrow) + wv;                   // or panel vector
+  const bool on = tail ? q < 2 * p : i > j && i < n;
+  if (!tail && TMR * (rb + blk) + TMR - 1 <= j) return;    // no rows: the whole workgroup
+  const double* row = (!on ? a.A + (size_t)(j + 1) * n
+                       : !tail ? a.A + (size_t)i * n
+                       : q < p ? a.W + (size_t)q * n : a.V + (size_t)(q - p) * n) + j + 1;
+  // the first 1024 columns, and column j with its partial sums
+  double r[16];
+#pragma unroll
+  for (int t = 0; t < 16; ++t) r[t] = row[min(lane + 64 * t, len - 1)];
+  const double x0 = a.col[j + 1], b0 = a.bq[j + 1];
+  const double pn = a.pn[min(lane, npn - 1)], pb = a.pb[min(lane, npn - 1)];
+  constexpr int PT = PINV_MAX_N / (64 * TMR);
+  double cl[PT];
+#pragma unroll
+  for (int u = 0; u < PT; ++u) cl[u] = a.col[j + 1 + min(tid + 64 * TMR * u, len - 1)];
+  const double sig2 = wave_sum(lane < npn ? pn : 0.0), cb = wave_sum(lane < npn ? pb : 0.0);
   double t, beta, sc;
-  if (sig2 == 0.0) { t = 0.0; beta = alpha; sc = 0.0; }
+  if (sig2 == 0.0) { t = 0.0; beta = x0; sc = 0.0; }
   else {
-    beta = -copysign(sqrt(alpha * alpha + sig2), alpha);
-    t = (beta - alpha) / beta;
-    sc = 1.0 / (alpha - beta);
+    beta = -copysign(sqrt(x0 * x0 + sig2), x0);
+    t = (beta - x0) / beta;
+    sc = 1.0 / (x0 - beta);
   }
-  if (tid == 0) { a.e[j] = beta; a.tau[j] = t; }
-  double v[TPT];
-  double pb = 0.0;
 #pragma unroll
-  for (int u = 0; u < TPT; ++u) {
-    const int i = j + tid + TBS * u;
-    double vi = 0.0;
-    if (i == j + 1) vi = 1.0;
-    else if (i > j + 1 && i < n) vi = col[u] * sc;
-    v[u] = vi;
-    if (i > j && i < n) {
+  for (int u = 0; u < PT; ++u) {
+    const int k = tid + 64 * TMR * u;
+    vs[k] = k == 0 ? 1.0 : k < len ? cl[u] * sc : 0.0;
+  }
+  __syncthreads();
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  for (int c = 0; c < len; c += 1024) {
+    double x[16];
+    if (c + 1024 < len) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = row[min(c + 1024 + lane + 64 * u, len - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; u += 4) {
+      const double* v = vs + c + lane + 64 * u;
+      s0 = fma(r[u], v[0], s0);
+      s1 = fma(r[u + 1], v[64], s1);
+      s2 = fma(r[u + 2], v[128], s2);
+      s3 = fma(r[u + 3], v[192], s3);
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) r[u] = x[u];
+  }
+  const double y = wave_sum((s0 + s1) + (s2 + s3));
+  if (tail) {
+    if (on && lane == 0) a.s12[q < p ? q : TNB + q - p] = y;
+    return;
+  }
+  if (lane == 0) {
+    const double vi = on ? vs[i - j - 1] : 0.0;
+    if (on) {
+      a.y[i] = y;
       a.V[(size_t)p * n + i] = vi;
       a.A[(size_t)j * n + i] = vi;
-      pb += vi * bq_[u];
     }
+    pdw[wv] = vi * y;
   }
-  const double vb = t * block_sum(pb, red);
-#pragma unroll
-  for (int u = 0; u < TPT; ++u) {
-    const int i = j + tid + TBS * u;
-    if (i > j && i < n) a.bq[i] = bq_[u] - vb * v[u];
-  }
-  // s1[q] = W[q] . v, s2[q] = V[q] . v over rows > j, q < p: thread group
-  // g (32 threads) owns one of the 2p values and strides over the rows, so
-  // every load is coalesced within the group and each value needs a single
-  // 32-lane reduction; v and the finalised column p - 1 come from LDS
-  if (p > 0) {
-#pragma unroll
-    for (int u = 0; u < TPT; ++u) {
-      const int i = j + tid + TBS * u;
-      if (i < n) { vsh[i - j] = v[u]; wsh[i - j] = wl[u]; vlsh[i - j] = vl[u]; }
-    }
-    __syncthreads();
-    // 32 groups of 32 threads; each of the 2p values gets gpv groups that
-    // split its rows; four independent accumulators keep loads in flight
-    const int grp = tid >> 5, gl = tid & 31;
-    const int nval = 2 * p, gpv = nval >= 32 ? 1 : 32 / nval;
-    const int val = grp / gpv, sub = grp % gpv;
-    double acc = 0.0;
-    if (val < nval) {
-      const bool isw = val < p;
-      const int q = isw ? val : val - p;
-      const double* colp = (isw ? a.W : a.V) + (size_t)q * n;
-      const double* xs = (q == p - 1) ? (isw ? wsh : vlsh) : nullptr;
-      const int stride = 32 * gpv;
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-      int i = j + 1 + sub * 32 + gl;
-      for (; i + 3 * stride < n; i += 4 * stride) {
-        const double x0 = xs ? xs[i - j] : colp[i];
-        const double x1 = xs ? xs[i + stride - j] : colp[i + stride];
-        const double x2 = xs ? xs[i + 2 * stride - j] : colp[i + 2 * stride];
-        const double x3 = xs ? xs[i + 3 * stride - j] : colp[i + 3 * stride];
-        a0 = fma(x0, vsh[i - j], a0);
-        a1 = fma(x1, vsh[i + stride - j], a1);
-        a2 = fma(x2, vsh[i + 2 * stride - j], a2);
-        a3 = fma(x3, vsh[i + 3 * stride - j], a3);
-      }
-      for (; i < n; i += stride) a0 = fma(xs ? xs[i - j] : colp[i], vsh[i - j], a0);
-      acc = (a0 + a1) + (a2 + a3);
-#pragma unroll
-      for (int m = 16; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 32);
-    }
-    if (gl == 0) gpart[grp] = acc;
-    __syncthreads();
-    if (tid < nval) {
-      double r = 0.0;
-      for (int k = 0; k < gpv; ++k) r += gpart[tid * gpv + k];
-      a.s12[tid < p ? tid : TNB + (tid - p)] = r;
-    }
-  }
-}
-
-// Rows i > j, one wavefront per row: g[i] = (A v)[i] - sum_{q<p} V_q[i] s1[q]
-// + W_q[i] s2[q]; per-workgroup partial dots g.v; and, when the next column
-// is in the same panel, its entries pc[i] = A[i][j+1] - sum_{q<p} (V_q[i]
-// W_q[j+1] + W_q[i] V_q[j+1]).
-__global__ __launch_bounds__(256) void k_tri_gemv(TriArgs a, int j, int p, int want_pc) {
-  __shared__ double pdw[4];
-  const int n = a.n, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int i = j + 1 + blockIdx.x * 4 + wv;
-  const double* v = a.V + (size_t)p * n;
-  double dot = 0.0;
-  if (i < n) {
-    const double* row = a.A + (size_t)i * n;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int c = j + 1 + lane;
-    // sixteen loads in flight per step, then eight, four, one; element t of
-    // this lane goes to accumulator t % 4 in every wide step, so the sums
-    // are those of the narrower steps alone
-    for (; c + 960 < n; c += 1024) {
-      double r[16], x[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) { r[q] = row[c + 64 * q]; x[q] = v[c + 64 * q]; }
-#pragma unroll
-      for (int q = 0; q < 16; q += 4) {
-        s0 = fma(r[q], x[q], s0); s1 = fma(r[q + 1], x[q + 1], s1);
-        s2 = fma(r[q + 2], x[q + 2], s2); s3 = fma(r[q + 3], x[q + 3], s3);
-      }
-    }
-    for (; c + 448 < n; c += 512) {
-      double r[8], x[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) { r[q] = row[c + 64 * q]; x[q] = v[c + 64 * q]; }
-      s0 = fma(r[0], x[0], s0); s1 = fma(r[1], x[1], s1); s2 = fma(r[2], x[2], s2); s3 = fma(r[3], x[3], s3);
-      s0 = fma(r[4], x[4], s0); s1 = fma(r[5], x[5], s1); s2 = fma(r[6], x[6], s2); s3 = fma(r[7], x[7], s3);
-    }
-    for (; c + 192 < n; c += 256) {
-      const double r0 = row[c], r1 = row[c + 64], r2 = row[c + 128], r3 = row[c + 192];
-      const double v0 = v[c], v1 = v[c + 64], v2 = v[c + 128], v3 = v[c + 192];
-      s0 = fma(r0, v0, s0); s1 = fma(r1, v1, s1); s2 = fma(r2, v2, s2); s3 = fma(r3, v3, s3);
-    }
-    for (; c < n; c += 64) s0 = fma(row[c], v[c], s0);
-    double corr = 0.0, pcc = 0.0;
-    if (lane < p) {
-      const double vq = a.V[(size_t)lane * n + i], wq = a.W[(size_t)lane * n + i];
-      corr = vq * a.s12[lane] + wq * a.s12[TNB + lane];
-      if (want_pc)
-        pcc = vq * a.W[(size_t)lane * n + j + 1] + wq * a.V[(size_t)lane * n + j + 1];
-    }
-    const double gi = wave_sum(((s0 + s1) + (s2 + s3)) - corr);
-    if (want_pc) {
-      const double pcs = wave_sum(pcc);
-      if (lane == 0) a.pc[i] = row[j + 1] - pcs;
-    }
-    if (lane == 0) a.g[i] = gi;
-    dot = gi * v[i];
-  }
-  if (lane == 0) pdw[wv] = dot;
   __syncthreads();
-  if (threadIdx.x == 0) a.pd[blockIdx.x] = (pdw[0] + pdw[1]) + (pdw[2] + pdw[3]);
-}
-
-// last column of a panel: w = tau g + alpha v over rows i > jp
-__global__ __launch_bounds__(TBS) void k_tri_fin(TriArgs a, int jp, int pp, int npd) {
-  __shared__ double red[TBS / 64];
-  const int n = a.n, tid = threadIdx.x;
-  const double tp = a.tau[jp];
-  double sp = 0.0;
-  for (int k = tid; k < npd; k += TBS) sp += a.pd[k];
-  const double alpha = -0.5 * tp * tp * block_sum(sp, red);
-  const double* v = a.V + (size_t)pp * n;
-  for (int i = jp + 1 + tid; i < n; i += TBS) a.W[(size_t)pp * n + i] = tp * a.g[i] + alpha * v[i];
+  if (tid == 0) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < TMR; ++w) s += pdw[w];
+    a.pd[rb + blk - (j + 1) / TMR] = s;
+    if (TMR * (rb + blk) <= j + 1) {       // the workgroup of row j + 1
+      a.tau[j] = t;
+      a.e[j] = beta;
+      a.scal[1] = t * (b0 + sc * cb);
+    }
+  }
 }
 
 // A[i][c] -= sum_q V[q][i] W[q][c] + W[q][i] V[q][c], i, c >= j1: 64 x 64
@@ -823,28 +772,32 @@ __global__ __launch_bounds__(DCB) void k_dc_down_post(DcArgs a, int lev) {
 static int pinv_forward(int n, const double* T, const double* b, const PinvWs& w, int nmax,
                         double cutoff, uint32_t* status, hipStream_t s, DcArgs& da,
                         std::vector<size_t>& ubase) {
-  TriArgs ta{w.A, w.V, w.W, w.tau, w.d, w.e, w.bq, w.g, w.s12, w.pc, w.pd, n};
+  // the partial sums of column norms (one per 64 rows) use merge scratch
+  TriArgs ta{w.A, w.V, w.W, w.tau, w.d, w.e, w.bq, w.y, w.s12, w.col, w.pd, w.es, w.dl, w.scal, n};
   const size_t nn = (size_t)n * n;
   k_pinv_copy<<<(unsigned)((nn + 255) / 256), 256, 0, s>>>(T, w.A, nn, b, w.bq, n);
   MINSR_CHECK_LAUNCH();
   // 1. tridiagonalisation
-  int npd = 0;
+  k_tri_row<0><<<(unsigned)((n + 63) / 64), 64, 0, s>>>(ta, -1, -1, 0);
+  MINSR_CHECK_LAUNCH();
   for (int j0 = 0; j0 < n; j0 += TNB) {
     const int nb = std::min(TNB, n - j0);
-    for (int p = 0; p < nb; ++p) {
-      const int j = j0 + p;
-      k_tri_col<<<1, TBS, 0, s>>>(ta, j, p, npd);
+    for (int p = 0; p < nb && j0 + p < n - 1; ++p) {
+      const int j = j0 + p, rows = n - j - 1;
+      const int rb = (j + 1) / (8 * TMR) * 8, nrow = (n + TMR - 1) / TMR - rb;
+      k_tri_mv<<<(unsigned)(nrow + (2 * p + TMR - 1) / TMR), 64 * TMR, 0, s>>>(ta, j, p, rb, nrow,
+                                                                               (rows + 64) / 64);
       MINSR_CHECK_LAUNCH();
-      if (j < n - 1) {
-        npd = (n - j - 1 + 3) / 4;
-        k_tri_gemv<<<(unsigned)npd, 256, 0, s>>>(ta, j, p, p + 1 < nb ? 1 : 0);
-        MINSR_CHECK_LAUNCH();
-      }
+      const unsigned grid = (unsigned)((rows + 63) / 64);
+      const int npd = (n + TMR - 1) / TMR - (j + 1) / TMR;
+      if (p == 0) k_tri_row<0><<<grid, 64, 0, s>>>(ta, j, p, npd);
+      else if (p <= 4) k_tri_row<4><<<grid, 64, 0, s>>>(ta, j, p, npd);
+      else if (p <= 8) k_tri_row<8><<<grid, 64, 0, s>>>(ta, j, p, npd);
+      else k_tri_row<16><<<grid, 64, 0, s>>>(ta, j, p, npd);
+      MINSR_CHECK_LAUNCH();
     }
     const int j1 = j0 + nb;
     if (j1 < n) {
-      k_tri_fin<<<1, TBS, 0, s>>>(ta, j1 - 1, nb - 1, npd);
-      MINSR_CHECK_LAUNCH();
       const unsigned tiles = (unsigned)((n - j1 + 63) / 64);
       k_tri_syr2k<<<dim3(tiles, tiles), 256, 0, s>>>(w.A, w.V, w.W, n, j1, nb);
       MINSR_CHECK_LAUNCH();
