@@ -28,7 +28,8 @@
 // read and 1.4 written), against 42.0 in k_jacobian.  It wins at every size:
 // 7 x 6, Ns = 33: d_h = 32 0.25 / 0.45 ms with the evaluation, d_h = 64 0.43 /
 // 1.11, d_h = 128 0.82 / 2.02; FP64 chain of 40, Ns = 33: d_h = 16 0.19 / 0.42,
-// d_h = 64 0.46 / 1.35.
+// d_h = 64 0.46 / 1.35.  FP64 d_h = 8, 256 samples: 7 x 6 0.16 / 0.45, chain of
+// 40 0.11 / 0.33.
 #pragma once
 
 #include <cmath>
@@ -137,52 +138,54 @@ __device__ inline void head_adjoint(int seed, int sk, const T (&hd)[4], T& dz0, 
 
 // ------------------------------------------------------------ reverse pass
 // Order of the reverse product's 3 H inputs (gate, i): the rows i are dealt in
-// groups of V to NC = 4 P chains (part of the rows, group mod 4); inside a
+// groups of V to NC = 4 P chains (part of the rows, group mod 4; d_h = 8: two
+// a part); inside a
 // group i runs over its V rows with the gates innermost.  Input e of chain c
 // is element e % 4 of K-step (e / 4) NC + c, so that consecutive products
 // belong to different chains.
 template <typename T, int H, int P> struct RevOrder {
-  static constexpr int V = MM<T>::V, NC = 4 * P, NS = 3 * H / (4 * NC);
+  static constexpr int V = MM<T>::V, CP = H < 16 ? 2 : 4, NC = CP * P, NS = 3 * H / (4 * NC);
   static constexpr int PITCH = 3 * H / 4 + V;
   static_assert(NS * 4 * NC == 3 * H && NS >= 1, "whole K-steps per chain");
   __device__ static void slot(int g, int i, int& step, int& el) {
     const int i4 = i / V, p = i4 / (H / P / V);
-    const int within = (i4 - p * (H / P / V)) >> 2;
+    const int within = (i4 - p * (H / P / V)) / CP;
     const int e = within * 3 * V + 3 * (i % V) + g;
-    step = (e / 4) * NC + 4 * p + (i4 & 3);
+    step = (e / 4) * NC + CP * p + i4 % CP;
     el = e & 3;
   }
   __device__ static void input(int step, int el, int& g, int& i) {
     const int c = step % NC, e = (step / NC) * 4 + el;
     const int within = e / (3 * V), r = e % (3 * V);
     g = r % 3;
-    i = ((c / 4) * (H / P / V) + within * 4 + (c & 3)) * V + r / 3;
+    i = ((c / CP) * (H / P / V) + within * CP + c % CP) * V + r / 3;
   }
 };
 
 template <typename T, int H, int P>
 constexpr size_t jm_rev_smem(int dim, int Lx) {
   return sizeof(T) * ((size_t)64 * RevOrder<T, H, P>::PITCH +
-                      (dim == 2 ? mm_slot<T>(H) + (size_t)Lx * 4 * H * 4 : 0));
+                      (dim == 2 ? mm_slot<T>(H) + (size_t)Lx * 64 * mm_tiles(H) * mm_lane_units(H) : 0));
 }
 
 template <typename T, int H, int DIM, int P>
-__global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 ? 1 : 2) void k_jac_rev(JmArgs<T> a) {
+__global__ __launch_bounds__(64 * mm_tiles(H), sizeof(T) == 8 && H == 64 ? 1 : 2) void k_jac_rev(JmArgs<T> a) {
   using M = MM<T>;
   using acc_t = typename M::acc;
   using vec_t = typename M::vec;
   using R = RevOrder<T, H, P>;
-  constexpr int NW = H / 16, NT = 64 * NW, KT = H / 4, V = M::V;
+  constexpr int NW = mm_tiles(H), NT = 64 * NW, KT = H / 4, V = M::V;
+  constexpr int EU = mm_lane_units(H);   // units of a lane
   constexpr int KR = 3 * H / 4, PD = R::PITCH, PT = mm_pitch<T>(H);
   constexpr int NG = DIM == 2 ? 5 : 4;
   extern __shared__ __align__(16) unsigned char jsm[];
   T* D = reinterpret_cast<T*>(jsm);        // [4][16][PD] gate adjoints of a site
   T* X = D + 64 * PD;                      // 2D: [4][16][PT] adjoint of h'
-  T* pend = X + mm_slot<T>(H);             // 2D: [Lx][NT][4] from the row above, by column
+  T* pend = X + mm_slot<T>(H);             // 2D: [Lx][NT][EU] from the row above, by column
 
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int n = l & 15, q = l >> 4;
-  const int j0 = 16 * w + 4 * q;
+  const int j0 = mm_first<H>(w, q);
   const int N = a.N, Lx = a.Lx;
   const int ng = (a.ns + 15) / 16;
   const int seed = blockIdx.x / ng;
@@ -195,86 +198,90 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 ? 1 : 2) void k_ja
   T* ad = a.adj + ((size_t)seed * a.ns + sl) * N * NG * H + j0;
 
   // A operands: W_q^T rows (this wave's units), U1^T and U2^T rows
-  const int ja = 16 * w + M::row(n);
+  const int jt = mm_unit<T, H>(w, n), ja = min(jt, H - 1);
+  const bool arow = jt < H;
   T wr[KR], w1[DIM == 2 ? KT : 1], w2[DIM == 2 ? KT : 1];
 #pragma unroll
   for (int t = 0; t < KR; ++t) {
     int g, i;
     R::input(t, q, g, i);
-    wr[t] = a.w.bw[((size_t)(i / V) * H + ja) * 3 * V + g * V + i % V];
+    const T x = a.w.bw[((size_t)(i / V) * H + ja) * 3 * V + g * V + i % V];
+    wr[t] = arow ? x : (T)0;
   }
   if constexpr (DIM == 2) {
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
       const int i = 4 * t + q;
       const T* b = a.w.b2 + ((size_t)(i / V) * H + ja) * 2 * V + i % V;
-      w1[t] = b[0];
-      w2[t] = b[V];
+      w1[t] = arow ? b[0] : (T)0;
+      w2[t] = arow ? b[V] : (T)0;
     }
     for (int i = 0; i < Lx; ++i) {
-      const T z[4] = {(T)0, (T)0, (T)0, (T)0};
-      store4(pend + ((size_t)i * NT + tid) * 4, z);   // private to the thread
+      const T z[EU] = {};
+      store4(pend + ((size_t)i * NT + tid) * EU, z);   // private to the thread
     }
   }
-  // where this lane's 12 gate adjoints go
-  int off[3][4];
+  // where this lane's 3 EU gate adjoints go
+  int off[3][EU];
 #pragma unroll
   for (int g = 0; g < 3; ++g)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < EU; ++e) {
       int step, el;
       R::slot(g, j0 + e, step, el);
       off[g][e] = (el * 16 + n) * PD + step;
     }
-  T U0[4], U1[4];
+  T U0[EU], U1[EU];
   load4(a.w.head + (2 * seed) * H + j0, U0);
   load4(a.w.head + (2 * seed + 1) * H + j0, U1);
 
-  T carry[4] = {(T)0, (T)0, (T)0, (T)0};   // adjoint of h_{k} from site k + 1
+  T carry[EU] = {};         // adjoint of h_{k} from site k + 1
   // the site's tape (1D: and h_{k-1}), requested a site ahead
-  T t_[5][4], hdn[4];
+  T t_[5][EU], hdn[4];
   int skn;
   auto fetch = [&](int k) {
 #pragma unroll
     for (int g = 0; g < NG; ++g) load4(tp + ((size_t)k * NG + g) * H, t_[g]);
     if constexpr (DIM == 1) {
       if (k > 0) load4(a.states + ((size_t)(a.s_base + sl) * N + k - 1) * H + j0, t_[4]);
-      else t_[4][0] = t_[4][1] = t_[4][2] = t_[4][3] = (T)0;
+      else
+#pragma unroll
+        for (int e = 0; e < EU; ++e) t_[4][e] = (T)0;
     }
     load4(hd + 4 * k, hdn);
     skn = sg[k] & 1;
   };
   fetch(N - 1);
   for (int k = N - 1; k >= 0; --k) {
-    T u[4], r[4], ag[4], ht[4], x[4], hc[4];
+    T u[EU], r[EU], ag[EU], ht[EU], x[EU];
     const int sk = skn;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < EU; ++e) {
       u[e] = t_[0][e]; r[e] = t_[1][e]; ag[e] = t_[2][e]; ht[e] = t_[3][e]; x[e] = t_[4][e];
-      hc[e] = hdn[e];
     }
+    const T hc[4] = {hdn[0], hdn[1], hdn[2], hdn[3]};
     if (k > 0) fetch(k - 1);
     const int jr = DIM == 2 ? k / Lx : 0, kr = k - jr * Lx;
     const int col = (jr & 1) ? Lx - 1 - kr : kr;
     const bool hasV = DIM == 2 && jr > 0;
-    T* pc = pend + ((size_t)col * NT + tid) * 4;
+    T* pc = pend + ((size_t)col * NT + tid) * EU;
     T dz0, dz1;
     head_adjoint<T>(seed, sk, hc, dz0, dz1);
-    T in[4];
+    T in[EU];
     if constexpr (DIM == 2) {
       load4(pc, in);
       // the neighbour along the path adds to it, unless k + 1 starts a row
       if (kr + 1 < Lx) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) in[e] += carry[e];
+        for (int e = 0; e < EU; ++e) in[e] += carry[e];
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) in[e] = carry[e];
+      for (int e = 0; e < EU; ++e) in[e] = carry[e];
     }
-    T dpu[4], dpr[4], dg[4], da[4], dd[4];
+    T dpu[EU], dpr[EU], dg[EU], da[EU], dd[EU];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < EU; ++e) {
       T dh = dz0 * U0[e] + dz1 * U1[e];
       dh += in[e];
       const T dht = dh * u[e];
@@ -310,20 +317,21 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 ? 1 : 2) void k_ja
           c[(V * v + e) % R::NC] = M::mma(wr[V * v + e], xs[e], c[(V * v + e) % R::NC]);
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < EU; ++e)
 #pragma unroll
         for (int pt = 0; pt < P; ++pt)
-          dd[e] += (c[4 * pt][e] + c[4 * pt + 1][e]) + (c[4 * pt + 2][e] + c[4 * pt + 3][e]);
+          if constexpr (R::CP == 2) dd[e] += c[2 * pt][e] + c[2 * pt + 1][e];
+          else dd[e] += (c[4 * pt][e] + c[4 * pt + 1][e]) + (c[4 * pt + 2][e] + c[4 * pt + 3][e]);
     }
     if constexpr (DIM == 1) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) carry[e] = dd[e];
+      for (int e = 0; e < EU; ++e) carry[e] = dd[e];
       mm_sync<NW>();                       // D is rewritten at the next site
     } else {
       if (act) store4(ak + 4 * H, dd);
       if (k == 0) break;                   // no predecessors
 #pragma unroll
-      for (int e = 0; e < 4; ++e) X[(e * 16 + n) * PT + 4 * w + q] = dd[e];
+      for (int e = 0; e < EU; ++e) X[mm_place<T, H>(w, q, n, e)] = dd[e];
       mm_sync<NW>();
       // adjoints of the predecessors, a chain per part of the rows
       acc_t ch[P], cv[P];
@@ -341,9 +349,9 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 ? 1 : 2) void k_ja
           cv[pt] = M::mma(w2[t], xs[e], cv[pt]);
         }
       }
-      T v4[4];
+      T v4[EU];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < EU; ++e) {
         T sh = ch[0][e], sv = cv[0][e];
 #pragma unroll
         for (int pt = 1; pt < P; ++pt) { sh += ch[pt][e]; sv += cv[pt][e]; }
@@ -383,7 +391,8 @@ __global__ __launch_bounds__(256, 2) void k_jac_rows_mm(JmArgs<T> a) {
   using acc_t = typename M::acc;
   constexpr int TB = M::TB, KS = 64 / TB;              // sites per K-step
   constexpr int WT = H / TB >= 4 ? 2 : 1;              // tiles per side of a wave's block
-  constexpr int NB = H / (TB * WT);                    // blocks per side
+  constexpr int NB = H < TB ? 1 : H / (TB * WT);       // blocks per side
+  constexpr bool PAD = H < TB;                         // a tile wider than the model
   constexpr int NM = DIM == 2 ? 5 : 3, NG = DIM == 2 ? 5 : 4;
   constexpr int ds = DIM == 1 ? 2 : 4;
   constexpr int UB = 8;                                // K-steps requested together
@@ -396,6 +405,7 @@ __global__ __launch_bounds__(256, 2) void k_jac_rows_mm(JmArgs<T> a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kl = lane / TB, cl = lane % TB;
+  const int cm = PAD ? min(cl, H - 1) : cl;            // further rows and columns are not stored
   const size_t s = (size_t)a.s_base + sl;
   const Layout& L = a.L;
   const T sc = a.scale;
@@ -445,7 +455,7 @@ __global__ __launch_bounds__(256, 2) void k_jac_rows_mm(JmArgs<T> a) {
         const int k = N - 1 - (KS * (u0 + u) + kl), kc = max(k, 0);
         const int p = pm[kc];
         const bool on = k >= 0 && p >= 0;
-        const unsigned oa = (unsigned)(kc * (NG * H) + cl), ob = (unsigned)max(p, 0) * ldb + cl;
+        const unsigned oa = (unsigned)(kc * (NG * H) + cm), ob = (unsigned)max(p, 0) * ldb + cm;
 #pragma unroll
         for (int i = 0; i < WT; ++i) {
           const T xa = pa[oa + i * TB];
@@ -482,15 +492,16 @@ __global__ __launch_bounds__(256, 2) void k_jac_rows_mm(JmArgs<T> a) {
       for (int e = 0; e < M::E; ++e) {
         const unsigned at = ((jb * WT + i) * TB + M::row(e, kl)) * ldq + cl;
 #pragma unroll
-        for (int c = 0; c < WT; ++c) om[at + c * TB] = acc[i][c][e] * sc;
+        for (int c = 0; c < WT; ++c)
+          if (!PAD || (M::row(e, kl) < H && cl < H)) om[at + c * TB] = acc[i][c][e] * sc;
       }
   }
 
   // ---- biases, one-hot input columns and the head: thread j sums its unit
   // over the sites, last to first; job 0: u, 1: r, 2: candidate, 3: head
-  const int j = tid % H;
-  constexpr int NJ = 256 / H > 4 ? 4 : 256 / H;
-  for (int job = tid / H; job < 4 && tid / H < NJ; job += NJ) {
+  constexpr int JS = H < 64 ? 64 : H, NJ = 256 / JS;   // d_h <= 64: a wave per job
+  const int j = tid % JS;
+  for (int job = tid / JS; job < 4 && j < H; job += NJ) {
     T b = (T)0, b2 = (T)0, gx[ds];
 #pragma unroll
     for (int c = 0; c < ds; ++c) gx[c] = (T)0;
@@ -563,7 +574,7 @@ static int jm_chunk(const JmArgs<T>& a, hipStream_t s) {
   if (pairs > 65536) k_jac_head<T, H, 64><<<(unsigned)((pairs + 255) / 256), 256, 0, s>>>(a);
   else k_jac_head<T, H, 16><<<(unsigned)((pairs + 63) / 64), 256, 0, s>>>(a);
   MINSR_CHECK_LAUNCH();
-  k_jac_rev<T, H, DIM, P><<<seeds * (unsigned)((a.ns + 15) / 16), 4 * H,
+  k_jac_rev<T, H, DIM, P><<<seeds * (unsigned)((a.ns + 15) / 16), 64 * mm_tiles(H),
                             jm_rev_smem<T, H, P>(DIM, a.Lx), s>>>(a);
   MINSR_CHECK_LAUNCH();
   k_jac_rows_mm<T, H, DIM><<<seeds * (unsigned)a.ns, 256, a.N * (2 * sizeof(T) + 8), s>>>(a);

@@ -10,6 +10,12 @@ namespace minsr {
 typedef __attribute__((ext_vector_type(4))) float f32x4r;
 typedef __attribute__((ext_vector_type(4))) double f64x4r;
 
+// Tiles of 16 units of a hidden width, and the units of a lane in a tile's
+// result: four, or two at d_h = 8, where the eight rows that are left have
+// zero weights and land in result elements that nothing reads.
+__host__ __device__ constexpr int mm_tiles(int H) { return (H + 15) / 16; }
+__host__ __device__ constexpr int mm_lane_units(int H) { return H < 16 ? 2 : 4; }
+
 // Lane l of a product: A[l % 16][l / 16], B[l / 16][l % 16]; result element v
 // is unit 4 (l / 16) + v of the tile, column l % 16 (the FP64 result rows are
 // permuted to that by the order of the A rows).  Both instructions add their
@@ -36,7 +42,7 @@ template <> struct MM<double> {
   }
 };
 
-// four consecutive values as one (FP64: two) 16-byte accesses
+// a lane's consecutive units as one (FP64: two, d_h = 8 one) 16-byte accesses
 __device__ inline void load4(const float* p, float (&v)[4]) {
   const float4 x = *reinterpret_cast<const float4*>(p);
   v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
@@ -51,6 +57,14 @@ __device__ inline void store4(float* p, const float (&v)[4]) {
 __device__ inline void store4(double* p, const double (&v)[4]) {
   *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
   *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
+}
+
+__device__ inline void load4(const double* p, double (&v)[2]) {
+  const double2 x = *reinterpret_cast<const double2*>(p);
+  v[0] = x.x; v[1] = x.y;
+}
+__device__ inline void store4(double* p, const double (&v)[2]) {
+  *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
 }
 
 // workgroup barrier ordering shared memory only; a single wave needs a fence
@@ -69,6 +83,16 @@ template <int NW> __device__ inline void mm_sync() {
 // reads of a quarter wave and the writes fall on different banks
 template <typename T> constexpr int mm_pitch(int H) { return H / 4 + MM<T>::V; }
 template <typename T> constexpr size_t mm_slot(int H) { return (size_t)64 * mm_pitch<T>(H); }
+// first unit of a lane (wave w, lane group q); unit of A row r of a wave's
+// tile, H or above: none; place of a lane's unit e in such a vector
+template <int H> __device__ inline int mm_first(int w, int q) { return H < 16 ? 2 * q : 16 * w + 4 * q; }
+template <typename T, int H> __device__ inline int mm_unit(int w, int r) {
+  return H < 16 ? 2 * (r & 3) + (r >> 2) + (r >> 3) * H : 16 * w + MM<T>::row(r);
+}
+template <typename T, int H> __device__ inline int mm_place(int w, int q, int n, int e) {
+  return H < 16 ? ((2 * (q & 1) + e) * 16 + n) * mm_pitch<T>(H) + (q >> 1)
+                : (e * 16 + n) * mm_pitch<T>(H) + 4 * w + q;
+}
 
 constexpr size_t MM_LDS = 160 * 1024;
 

@@ -30,7 +30,8 @@
 // (RM_ELOC_SPLIT), 9 x 9, d_h = 128, 1024 samples 16.1 -> 7.9 ms against a
 // kernel of 32 sequences and one wave a SIMD that streamed U1 | U2 from L2 and
 // kept its window of states in global memory (56k cycles a site of 32, a third
-// of them its work); here about 14k a site of 16 (products 5.5k).
+// of them its work); here about 14k a site of 16 (products 5.5k).  FP64 7 x 6,
+// d_h = 8, 256 samples: evaluation 133 -> 84 us, local energies 1082 -> 206.
 #pragma once
 
 #include <mutex>
@@ -109,19 +110,20 @@ template <typename T> struct RecShape {
   static size_t bytes(int H, int dim, int Lx, int N, int mode) {
     const int ds = dim == 1 ? 2 : 4;
     const size_t t = (size_t)(3 * ds + 8) * H + mm_slot<T>(H) * slots(dim, Lx) +
-                     (size_t)2 * rec_batch<T>(mode) * (H / 16) * 64;
+                     (size_t)2 * rec_batch<T>(mode) * mm_tiles(H) * 64;
     return t * sizeof(T) + 16 * 4 * 8 + (size_t)16 * N + 64 + (3 * H + 16) * sizeof(float);
   }
 };
 
 template <typename T, int H, int DIM, int MODEX>
-__global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 2) void k_rec_mm(RecArgs<T> a) {
+__global__ __launch_bounds__(64 * mm_tiles(H), sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 2) void k_rec_mm(RecArgs<T> a) {
   using M = MM<T>;
   using acc_t = typename M::acc;
   using vec_t = typename M::vec;
   constexpr bool SPLIT = MODEX == RM_ELOC_SPLIT;
   constexpr int MODE = SPLIT ? RM_ELOC : MODEX;
-  constexpr int NW = H / 16, NT = 64 * NW, KT = H / 4, V = M::V;
+  constexpr int NW = mm_tiles(H), NT = 64 * NW, KT = H / 4, V = M::V;
+  constexpr int EU = mm_lane_units(H);
   constexpr int ds = DIM == 1 ? 2 : 4;
   constexpr int PT = mm_pitch<T>(H);
   constexpr size_t SLOT = mm_slot<T>(H);
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int n = l & 15, q = l >> 4;
   const int N = a.N, Lx = a.Lx;
-  const int j0 = 16 * w + 4 * q;                     // this lane's units j0 .. j0 + 3
+  const int j0 = mm_first<H>(w, q);                  // this lane's units j0 .. j0 + EU - 1
   auto sync = [&]() { mm_sync<NW>(); };
 
   // which term and samples (local energies), or the 16 samples of the block
@@ -188,7 +190,8 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
     }
   }
   // A operands: row n of this wave's tile, input 4 t + q of step t
-  const int ja = 16 * w + M::row(n);
+  const int jt = mm_unit<T, H>(w, n), ja = min(jt, H - 1);
+  const bool arow = jt < H;
   constexpr int KF = H / 32;
   T wg[SPLIT ? 1 : 3][KT], wu[DIM == 2 ? 2 * KT : 1];
   mf16::h16x8 wh[SPLIT ? 3 : 1][SPLIT ? KF : 1], wl[SPLIT ? 3 : 1][SPLIT ? KF : 1];
@@ -224,7 +227,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
       const int k = 4 * t + q;
       const T* p = a.w.fw + ((size_t)(k / V) * H + ja) * 3 * V + k % V;
 #pragma unroll
-      for (int g = 0; g < 3; ++g) wg[g][t] = p[g * V];
+      for (int g = 0; g < 3; ++g) wg[g][t] = arow ? p[g * V] : (T)0;
     }
   }
   if constexpr (DIM == 2) {
@@ -232,15 +235,16 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
 #pragma unroll
     for (int t = 0; t < 2 * KT; ++t) {
       const int z = 4 * t + q, k = V * (z / (2 * V)) + z % V, u = (z / V) & 1;
-      wu[t] = a.w.f2[((size_t)(k / V) * H + ja) * 2 * V + u * V + k % V];
+      const T x = a.w.f2[((size_t)(k / V) * H + ja) * 2 * V + u * V + k % V];
+      wu[t] = arow ? x : (T)0;
     }
   }
 
   // states the walk starts from
-  T hp[4] = {(T)0, (T)0, (T)0, (T)0};                // 1D: the lane's units of h_{k-1}
-  auto put = [&](T* slot, const T (&v)[4]) {
+  T hp[EU] = {};                                     // 1D: the lane's units of h_{k-1}
+  auto put = [&](T* slot, const T (&v)[EU]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) slot[(e * 16 + n) * PT + 4 * w + q] = v[e];
+    for (int e = 0; e < EU; ++e) slot[mm_place<T, H>(w, q, n, e)] = v[e];
   };
   const int kstart = k0 + 1;
   if constexpr (DIM == 1) {
@@ -252,7 +256,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
     for (int i = 0; i < Lx; ++i) {
       int p = jr * Lx + ((jr & 1) ? Lx - 1 - i : i);
       if (p > k0) p = 2 * jr * Lx - 1 - p;           // the site above, if any
-      T v[4] = {(T)0, (T)0, (T)0, (T)0};
+      T v[EU] = {};
       if (p >= 0) load4(a.states_in + ((size_t)sid * N + p) * H + j0, v);
       put(X + SLOT * i, v);
     }
@@ -410,7 +414,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
         old_ph = so[4 * ks + 2 + vo];
       }
     int sh = -1, sv = -1;
-    T hin[4];
+    T hin[EU];
     T* xin;
     T* out;
     if constexpr (DIM == 2) {
@@ -463,7 +467,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
         }
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) hin[e] = acc[e];
+      for (int e = 0; e < EU; ++e) hin[e] = acc[e];
       if constexpr (SPLIT) {
         // h' is not bounded: the site's largest |h'| sets a power-of-two scale
         store4(XI + n * (H + 4) + j0, hin);
@@ -483,14 +487,14 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
       xin = X + SLOT * (k & 1);
       out = X + SLOT * ((k + 1) & 1);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) hin[e] = hp[e];
+      for (int e = 0; e < EU; ++e) hin[e] = hp[e];
     }
 
     // gate pre-activations: bias and spin-input columns first
-    acc_t ga[3];
-    T ai[4];
+    acc_t ga[3] = {};
+    T ai[EU];
     {
-      T b[4], x[4];
+      T b[EU], x[EU];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         load4(bias + g * H + j0, b);
@@ -499,16 +503,16 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
           if (sh >= 0) {
             load4(xc + (gx * ds + sh) * H + j0, x);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) b[e] += x[e];
+            for (int e = 0; e < EU; ++e) b[e] += x[e];
           }
           if (DIM == 2 && sv >= 0) {
             load4(xc + (gx * ds + (DIM == 2 ? 2 : 0) + sv) * H + j0, x);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) b[e] += x[e];
+            for (int e = 0; e < EU; ++e) b[e] += x[e];
           }
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < EU; ++e) {
           if (g < 3) ga[g][e] = b[e];
           else ai[e] = b[e];
         }
@@ -556,9 +560,9 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
           for (int g = 0; g < 3; ++g) ga[g] = M::mma(wg[g][V * tv + e], xs[e], ga[g]);
       }
     }
-    T hn[4], gu[4], gr[4], ag[4], gt[4];
+    T hn[EU], gu[EU], gr[EU], ag[EU], gt[EU];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < EU; ++e) {
       ag[e] = ga[2][e];
       if constexpr (SPLIT) {
         gu[e] = mf16::sigm_hw(ga[0][e]);
@@ -575,12 +579,13 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
     put(out, hn);
     // head: the lane's four units, the sequence's four lanes, the waves
     {
-      T u[4];
+      T u[EU];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         if (c >= 2 && !a.cplx) continue;
         load4(head + c * H + j0, u);
-        T z = (u[0] * hn[0] + u[1] * hn[1]) + (u[2] * hn[2] + u[3] * hn[3]);
+        T z = u[0] * hn[0] + u[1] * hn[1];
+        if constexpr (EU == 4) z = z + (u[2] * hn[2] + u[3] * hn[3]);
         z = xor32_sum(xor16_sum(z));
         if (q == 0) part[((size_t)(k % PR) * NW + w) * 64 + 4 * n + c] = z;
       }
@@ -598,7 +603,7 @@ __global__ __launch_bounds__(4 * H, sizeof(T) == 8 && H == 64 && DIM == 2 ? 1 : 
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) hp[e] = hn[e];
+    for (int e = 0; e < EU; ++e) hp[e] = hn[e];
     sync();
     const int jr = k / Lx, ir = (jr & 1) ? Lx - 1 - (k - jr * Lx) : k - jr * Lx;
     if constexpr (MODE == RM_SAMPLE) {
@@ -641,7 +646,7 @@ static size_t rec_smem(const minsr_model* m, int mode) {
 
 template <typename T>
 static bool rec_fits(const minsr_model* m) {
-  return !m->linear && m->H >= 16 && m->H <= (sizeof(T) == 4 ? 128 : 64) &&
+  return !m->linear && m->H >= (sizeof(T) == 4 ? 16 : 8) && m->H <= (sizeof(T) == 4 ? 128 : 64) &&
          rec_smem<T>(m, RM_EVAL) <= MM_LDS;   // the largest of the modes
 }
 
@@ -655,7 +660,7 @@ static int rec_launch(const RecArgs<T>& a, unsigned grid, size_t smem, hipStream
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)MM_LDS);
   });
   MINSR_HIP(attr);
-  k_rec_mm<T, H, DIM, MODE><<<grid, 4 * H, smem, s>>>(a);
+  k_rec_mm<T, H, DIM, MODE><<<grid, 64 * mm_tiles(H), smem, s>>>(a);
   MINSR_CHECK_LAUNCH();
   return MINSR_OK;
 }
@@ -665,6 +670,7 @@ static int rec_dispatch(const minsr_model* m, const RecArgs<T>& a, unsigned grid
   const size_t smem = rec_smem<T>(m, MODE);
   if (m->dim == 1) {
     switch (m->H) {
+      case 8: if constexpr (sizeof(T) == 8) return rec_launch<T, 8, 1, MODE>(a, grid, smem, s); break;
       case 16: return rec_launch<T, 16, 1, MODE>(a, grid, smem, s);
       case 32: return rec_launch<T, 32, 1, MODE>(a, grid, smem, s);
       case 64: return rec_launch<T, 64, 1, MODE>(a, grid, smem, s);
@@ -672,6 +678,7 @@ static int rec_dispatch(const minsr_model* m, const RecArgs<T>& a, unsigned grid
     }
   } else {
     switch (m->H) {
+      case 8: if constexpr (sizeof(T) == 8) return rec_launch<T, 8, 2, MODE>(a, grid, smem, s); break;
       case 16: return rec_launch<T, 16, 2, MODE>(a, grid, smem, s);
       case 32: return rec_launch<T, 32, 2, MODE>(a, grid, smem, s);
       case 64: return rec_launch<T, 64, 2, MODE>(a, grid, smem, s);
