@@ -967,8 +967,10 @@ static int eloc_t(minsr_model* m, const Work<T>& w, const minsr_hamiltonian* H, 
   }
   if (a.n_items > 0 && (which & 1)) {
     int rc;
-    // 2D: the state window in shared memory where it fits (d_h = 128: Lx <= 13)
-    if (!m->f64 && !m->force_vector && m->dim == 2 && rec_f32_fits(m) && M <= 1024)
+    // 2D: the state window in shared memory where it fits (d_h = 128: Lx <= 13);
+    // chains of 16 units, too narrow for the FP16 products (40 sites, 256
+    // samples, with the evaluation: 108 us, 255 with the vector recurrence)
+    if (!m->f64 && !m->force_vector && rec_f32_fits(m) && (m->dim == 2 ? M <= 1024 : m->H == 16))
       rc = launch_rec_eloc_f32(m, H, Ns, sigma, states, site, M, s);
     else if (!m->f64 && !m->force_vector && eloc_mfma_supported(m))
       rc = launch_eloc_mfma(m, H, Ns, sigma, states, site, M, s);

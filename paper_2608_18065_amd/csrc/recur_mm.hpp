@@ -733,7 +733,8 @@ static int rec_eloc(minsr_model* m, const Work<T>& w, const minsr_hamiltonian* H
   if constexpr (sizeof(T) == 4) {
     const size_t smem = rec_smem<T>(m, RM_ELOC_SPLIT);
     switch (m->H) {
-      case 16: return rec_launch<T, 16, 2, RM_ELOC>(a, grid, smem, s);
+      case 16: return m->dim == 1 ? rec_launch<T, 16, 1, RM_ELOC>(a, grid, smem, s)
+                                  : rec_launch<T, 16, 2, RM_ELOC>(a, grid, smem, s);
       case 32: return rec_launch<T, 32, 2, RM_ELOC_SPLIT>(a, grid, smem, s);
       case 64: return rec_launch<T, 64, 2, RM_ELOC_SPLIT>(a, grid, smem, s);
       case 128: return rec_launch<T, 128, 2, RM_ELOC_SPLIT>(a, grid, smem, s);
