@@ -13,9 +13,9 @@
 //      and the K x K matrix U of its non-deflated eigenvectors, and vectors
 //      are carried up (c = Z^T Q^T b) and down (y = Z t) the tree.
 //   3. t = c / w on the kept eigenvalues, y = Z t, x = Q y.
-// Each merge runs on one workgroup per node for the sequential parts (sort,
-// deflation scan, rotations) and on one wavefront per root or column for the
-// secular equations and eigenvectors.
+// Each merge runs on one workgroup per node for the sequential parts (deflation
+// scan, rotations), on a thread per entry for the order, and on one wavefront
+// per root, entry or column for the secular equations and eigenvectors.
 #include "model.hpp"
 #include <cmath>
 #include <vector>
@@ -504,8 +504,35 @@ __global__ __launch_bounds__(TBS) void k_dc_init(DcArgs a) {
 
 constexpr int DCB = 1024;   // workgroup of the per-node kernels
 
+// Ascending order of every node's children's eigenvalues (ties by index), one
+// entry per thread: m compares each, on as many compute units as there are 64
+// entries (inside k_dc_prep, on one: 1.1 of its 1.55 ms at 4096 entries).
+__global__ __launch_bounds__(64) void k_dc_rank(DcArgs a, int lev) {
+  extern __shared__ double ranked[];
+  const int tid = threadIdx.x, slot = blockIdx.y;
+  int lo, m;
+  node_of(a.n, lev, slot, lo, m);
+  const int i = blockIdx.x * 64 + tid;
+  if (m < 2 || (int)blockIdx.x * 64 >= m) return;
+  const double* ev = a.w.ev[(lev + 1) & 1] + lo;
+  for (int k = tid; k < m; k += 64) {
+    const double v = ev[k];
+    ranked[k] = v == v ? v : INFINITY;   // NaN ranks as +inf, so ranks stay a permutation
+  }
+  __syncthreads();
+  if (i >= m) return;
+  const double di = ranked[i];
+  int r = 0;
+#pragma unroll 8
+  for (int k = 0; k < m; ++k) {
+    const double dk = ranked[k];
+    r += (dk < di) || (dk == di && k < i);
+  }
+  a.w.perm[(size_t)lev * a.nmax + lo + r] = i;
+}
+
 // One workgroup per node of depth lev: gather the children's eigenvalues and
-// rank-one vector, sort, deflate (small z, then close pairs by a rotation),
+// rank-one vector in their order, deflate (small z, then close pairs by a rotation),
 // record the permutation, positions and rotations, and carry the first/last
 // rows and c into the node's basis up to the K x K block.
 __global__ __launch_bounds__(DCB) void k_dc_prep(DcArgs a, int lev) {
@@ -533,38 +560,21 @@ __global__ __launch_bounds__(DCB) void k_dc_prep(DcArgs a, int lev) {
   double* sd = sm;            // [m] d, sorted
   double* sz = sm + m;        // [m] z, sorted
   double* s3 = sm + 2 * m;    // [m] scratch
-  int* sidx = reinterpret_cast<int*>(sm + 3 * m);   // [m]
   const int m1 = m / 2;
   const double beta = w.es[lo + m1 - 1];
   const double rho = 2.0 * fabs(beta);
   const double sg = beta >= 0.0 ? 1.0 : -1.0;
-  int* perm = w.perm + (size_t)lev * a.nmax + lo;
+  const int* perm = w.perm + (size_t)lev * a.nmax + lo;
   int* wpos = w.wpos + (size_t)lev * a.nmax + lo;
   int* rotp = w.rotp + (size_t)lev * a.nmax + lo;
   int* rotn = w.rotn + (size_t)lev * a.nmax + lo;
   double* rotc = w.rotc + (size_t)lev * a.nmax + lo;
   double* rots = w.rots + (size_t)lev * a.nmax + lo;
-  // rank sort of the children's eigenvalues (ties by index)
-  for (int i = tid; i < m; i += DCB) {
-    const double v = w.ev[Pc][lo + i];
-    s3[i] = v == v ? v : INFINITY;     // NaN ranks as +inf, so ranks stay a permutation
-  }
-  __syncthreads();
-  for (int i = tid; i < m; i += DCB) {
-    const double di = s3[i];
-    int r = 0;
-    for (int k = 0; k < m; ++k) {
-      const double dk = s3[k];
-      r += (dk < di) || (dk == di && k < i);
-    }
-    sidx[r] = i;
-  }
-  __syncthreads();
   double mx = 0.0;
   for (int r = tid; r < m; r += DCB) {
-    const int i = sidx[r];
-    perm[r] = i;
-    sd[r] = s3[i];
+    const int i = perm[r];
+    const double v = w.ev[Pc][lo + i];
+    sd[r] = v == v ? v : INFINITY;
     const double zi = (i < m1 ? w.lr[Pc][lo + i] : sg * w.fr[Pc][lo + i]) * 0.70710678118654752440;
     sz[r] = zi;
     mx = fmax(mx, fmax(fabs(sd[r]), fabs(zi)));
@@ -705,25 +715,30 @@ __global__ __launch_bounds__(64 * SEC_WAVES) void k_dc_secular(DcArgs a, int lev
 
 // Gu-Eisenstat: |zhat_i|^2 = (lambda_{K-1} - d_i)/rho
 //   * prod_{j<i} (lambda_j - d_i)/(d_j - d_i) * prod_{i<=j<K-1} (lambda_j - d_i)/(d_{j+1} - d_i)
+// A wavefront per entry: the product's K divisions are a serial chain for one
+// thread (64 us a level of n = 4096, now 6).
 __global__ __launch_bounds__(256) void k_dc_zhat(DcArgs a, int lev) {
-  const int slot = blockIdx.y;
+  const int slot = blockIdx.y, lane = threadIdx.x & 63;
   int lo, m;
   node_of(a.n, lev, slot, lo, m);
   if (m < 2) return;
   const int K = a.w.kinfo[(size_t)lev * 4 * a.nmax + 2 * slot];
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= K) return;
   const double* dl = a.w.dl + lo;
   const double* dlo = a.w.dlo + lo;
   const double* ta = a.w.taus + lo;
   const double di = dl[i];
-  double prod = ((dlo[K - 1] - di) + ta[K - 1]) / a.w.rho[lo];
-  for (int j = 0; j < K - 1; ++j) {
+  double prod = 1.0;
+  for (int j = lane; j < K - 1; j += 64) {
     const double num = (dlo[j] - di) + ta[j];
     const double den = (j < i ? dl[j] : dl[j + 1]) - di;
     prod *= num / den;
   }
-  a.w.zh[lo + i] = copysign(sqrt(fmax(prod, 0.0)), a.w.wv[lo + i]);
+#pragma unroll
+  for (int q = 32; q >= 1; q >>= 1) prod *= __shfl_xor(prod, q, 64);
+  prod *= ((dlo[K - 1] - di) + ta[K - 1]) / a.w.rho[lo];
+  if (lane == 0) a.w.zh[lo + i] = copysign(sqrt(fmax(prod, 0.0)), a.w.wv[lo + i]);
 }
 
 // eigenvector columns of the non-deflated block: u_k = zhat_k / (d_k - lambda_col),
@@ -781,25 +796,37 @@ __global__ __launch_bounds__(TBS) void k_dc_root(DcArgs a) {
 }
 
 // down the tree, node at depth lev: tk = U t (k < K), then working order,
-// rotations in reverse, scatter to the children's positions
+// rotations in reverse, scatter to the children's positions.  64 entries a
+// workgroup, the columns dealt to its four wavefronts, eight loads in flight
+// (one thread an entry, one load after the other: 106 us a level, now 10).
 __global__ __launch_bounds__(256) void k_dc_down_gemv(DcArgs a, int lev) {
-  const int slot = blockIdx.y;
+  __shared__ double part[4][64];
+  const int slot = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int lo, m;
   node_of(a.n, lev, slot, lo, m);
-  if (m < 2) return;
+  if (m < 2 || (int)blockIdx.x * 64 >= m) return;
   const int K = a.w.kinfo[(size_t)lev * 4 * a.nmax + 2 * slot];
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= m) return;
+  const int k = blockIdx.x * 64 + lane;
   const double* t = a.w.tv[lev & 1] + lo;
-  double s;
+  double s = 0.0;
   if (k < K) {
-    const double* U = a.w.U + a.ubase + (size_t)slot * a.umm;
-    s = 0.0;
-    for (int c = 0; c < K; ++c) s = fma(U[(size_t)c * K + k], t[c], s);
-  } else {
-    s = t[k];
+    const double* U = a.w.U + a.ubase + (size_t)slot * a.umm + k;
+    for (int c0 = wv; c0 < K; c0 += 32) {
+      double u[8], x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int c = min(c0 + 4 * q, K - 1);
+        u[q] = U[(size_t)c * K];
+        x[q] = t[c];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s = c0 + 4 * q < K ? fma(u[q], x[q], s) : s;
+    }
   }
-  a.w.tk[lo + k] = s;
+  part[wv][lane] = s;
+  __syncthreads();
+  if (wv == 0 && k < m)
+    a.w.tk[lo + k] = k < K ? (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]) : t[k];
 }
 
 __global__ __launch_bounds__(DCB) void k_dc_down_post(DcArgs a, int lev) {
@@ -889,13 +916,15 @@ static int pinv_forward(int n, const double* T, const double* b, const PinvWs& w
     const size_t mm = mmax_of(n, lev);
     da.umm = mm * mm;
     const unsigned nodes = 1u << lev;
-    const size_t shm_prep = mm * 3 * sizeof(double) + mm * sizeof(int);
+    const size_t shm_prep = mm * 3 * sizeof(double);
+    k_dc_rank<<<dim3((unsigned)((mm + 63) / 64), nodes), 64, mm * sizeof(double), s>>>(da, lev);
+    MINSR_CHECK_LAUNCH();
     k_dc_prep<<<nodes, DCB, shm_prep, s>>>(da, lev);
     MINSR_CHECK_LAUNCH();
     k_dc_secular<<<dim3((unsigned)((mm + SEC_WAVES - 1) / SEC_WAVES), nodes), 64 * SEC_WAVES,
                    mm * 2 * sizeof(double), s>>>(da, lev);
     MINSR_CHECK_LAUNCH();
-    k_dc_zhat<<<dim3((unsigned)((mm + 255) / 256), nodes), 256, 0, s>>>(da, lev);
+    k_dc_zhat<<<dim3((unsigned)((mm + 3) / 4), nodes), 256, 0, s>>>(da, lev);
     MINSR_CHECK_LAUNCH();
     k_dc_ucols<<<dim3((unsigned)((mm + 3) / 4), nodes), 256, 0, s>>>(da, lev);
     MINSR_CHECK_LAUNCH();
@@ -980,7 +1009,7 @@ int launch_pinv_solve(int n, double* T, double cutoff, const double* b, double* 
     const size_t mm = mmax_of(n, lev);
     da.umm = mm * mm;
     const unsigned nodes = 1u << lev;
-    k_dc_down_gemv<<<dim3((unsigned)((mm + 255) / 256), nodes), 256, 0, s>>>(da, lev);
+    k_dc_down_gemv<<<dim3((unsigned)((mm + 63) / 64), nodes), 256, 0, s>>>(da, lev);
     MINSR_CHECK_LAUNCH();
     k_dc_down_post<<<nodes, DCB, mm * sizeof(double), s>>>(da, lev);
     MINSR_CHECK_LAUNCH();
