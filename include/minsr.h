@@ -418,7 +418,9 @@ int minsr_batch_destroy(minsr_batch* b);
 /* ---- launch parameters chosen by the autotuner ---------------------------
  * key "gram_split": split-K factor of the Gram (0 = built-in heuristic);
  * key "eloc_grid": workgroups of the persistent local-energy launch
- * (0 = one per work item up to the window limit);
+ * (0 = one per work item up to the window limit; the matrix-core recurrence,
+ * which serves FP64 models with d_h <= 64, 2D models and FP32 chains with
+ * d_h = 16, takes no notice of it);
  * key "sample_r": sequences per thread of the vector recurrence (1 or 4) that
  * then samples and evaluates; 0: the built-in choice between it and the
  * matrix-core recurrence (same results bit for bit; FP32 1D chains with

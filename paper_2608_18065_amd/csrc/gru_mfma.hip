@@ -1,5 +1,6 @@
 // Local energies of FP32 models on the matrix cores (Sec. 2.3, local
-// energy; App. A, GRU cells).
+// energy; App. A, GRU cells): chains with d_h >= 32, and 2D models whose state
+// window is too large for shared memory (recur_mm.hpp has the others).
 //
 // A workgroup re-evaluates 32 connected configurations that share their
 // first flipped site (one term of the Hamiltonian for 32 samples), so all

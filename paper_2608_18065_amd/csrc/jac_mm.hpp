@@ -22,7 +22,7 @@
 // as its partial sums (4 per part of the rows), the weight blocks from the
 // last site to the first.
 //
-// 10 x 10, d_h = 128, Ns = 4096 FP32: head 0.15 ms, reverse pass 0.93 (its
+// 10 x 10, d_h = 128, Ns = 4096 FP32: head 0.09 ms, reverse pass 0.93 (its
 // products' issue 0.42, two barriers and the tape's latency a site with one
 // workgroup a compute unit most of the rest), rows 1.34 (products 0.48; 3.3 GB
 // read and 1.4 written), against 42.0 in k_jacobian.  It wins at every size:
@@ -56,11 +56,31 @@ template <typename T> struct JmArgs {
 };
 
 // ------------------------------------------------------------ output head
+// sum over groups of W lanes in every lane, in the order of an xor butterfly
+// from W / 2 down (W = 8: up), on the VALU: a row's values repeat with the
+// distances already added, so a rotation reaches the partner's value
+template <int W, typename T> __device__ inline T unit_sum(T v) {
+  if constexpr (W == 64) v = xor32_sum(v);
+  if constexpr (W >= 32) v = xor16_sum(v);
+  if constexpr (W >= 16) {
+    v += row_lane<0x128>(v);                // rotated by 8
+    v += row_lane<0x124>(v);
+    v += row_lane<0x122>(v);
+    v += row_lane<0x121>(v);
+  } else {
+    v += row_lane<0xB1>(v);                 // quad_perm [1, 0, 3, 2]
+    v += row_lane<0x4E>(v);                 // quad_perm [2, 3, 0, 1]
+    v += row_lane<0x141>(v);                // row_half_mirror
+  }
+  return v;
+}
+
 // one wave per PW (sample, site) pairs: per pair the sums over the units as
 // k_jacobian forms them (an xor butterfly over 64 lanes, then the two
 // wavefronts' halves at d_h = 128), then lane i the conditional of pair i.
 // PW is 64, or 16 where that leaves SIMDs idle (640 pairs, d_h = 16: 12.9 ->
-// 6 us)
+// 5.2 us).  The sums stay on the VALU and eight states are requested
+// together: 10 x 10, d_h = 128, 4096 samples 153 -> 94 us.
 template <typename T, int H, int PW>
 __global__ __launch_bounds__(256) void k_jac_head(JmArgs<T> a) {
   constexpr int W = H < 64 ? H : 64, G = H / W;
@@ -78,29 +98,45 @@ __global__ __launch_bounds__(256) void k_jac_head(JmArgs<T> a) {
     for (int c = 0; c < 4; ++c) u[g][c] = c < nq ? a.w.head[c * H + g * W + j] : (T)0;
   const T* st = a.states + (size_t)a.s_base * a.N * H;
   T z[4] = {(T)0, (T)0, (T)0, (T)0};
-  for (int i0 = 0; i0 < PW; i0 += PP) {
-    const long long p = min(p0 + i0 + sub, np - 1);
-    T h[G];
+  constexpr int B = PW / PP < 8 ? PW / PP : 8;   // states requested together
+  for (int i0 = 0; i0 < PW; i0 += PP * B) {
+    T h[B][G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) h[g] = st[(size_t)p * H + g * W + j];
+    for (int b = 0; b < B; ++b) {
+      const long long p = min(p0 + i0 + PP * b + sub, np - 1);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (c >= nq) continue;
-      T t = (T)0;
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        T v = u[g][c] * h[g];
-#pragma unroll
-        for (int m = W / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-        t = g == 0 ? v : t + v;
-      }
-      // pair i0 + k's sum is in lanes k W ..; lane i0 + k keeps it
-#pragma unroll
-      for (int k = 0; k < PP; ++k) {
-        const T v = __shfl(t, k * W, 64);
-        if (lane == i0 + k) z[c] = v;
-      }
+      for (int g = 0; g < G; ++g) h[b][g] = st[(size_t)p * H + g * W + j];
     }
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (c >= nq) continue;
+        T t = (T)0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const T v = unit_sum<W>(u[g][c] * h[b][g]);
+          t = g == 0 ? v : t + v;
+        }
+        // pair i0 + PP b + k's sum is in lanes k W ..; that lane keeps it
+        const int at = lane - (i0 + PP * b);
+        const T s0 = wave_lane<0>(t);
+        if (at == 0) z[c] = s0;
+        if constexpr (PP >= 2) { const T v = wave_lane<W % 64>(t); if (at == 1) z[c] = v; }
+        if constexpr (PP >= 4) {
+          const T v2 = wave_lane<2 * W % 64>(t), v3 = wave_lane<3 * W % 64>(t);
+          if (at == 2) z[c] = v2;
+          if (at == 3) z[c] = v3;
+        }
+        if constexpr (PP >= 8) {
+          const T v4 = wave_lane<4 * W % 64>(t), v5 = wave_lane<5 * W % 64>(t);
+          const T v6 = wave_lane<6 * W % 64>(t), v7 = wave_lane<7 * W % 64>(t);
+          if (at == 4) z[c] = v4;
+          if (at == 5) z[c] = v5;
+          if (at == 6) z[c] = v6;
+          if (at == 7) z[c] = v7;
+        }
+      }
   }
   const long long p = p0 + lane;
   if (lane >= PW || p >= np) return;

@@ -1,5 +1,7 @@
 // Per-sample log-derivatives d log Psi(sigma^(s)) / d theta (Sec. 2.3,
-// Alg. 1 step 5) by a hand-written reverse pass through the GRU of App. A.
+// Alg. 1 step 5) by a hand-written reverse pass through the GRU of App. A: FP32
+// chains (d_h = 128 up to 128 sites: jac_mfma.hip), the shapes that jac_mm.hpp
+// does not take, and any model for which "jac_parts" asks for it.
 //
 // One workgroup owns SG samples.  Threads (p, j) of a sample own hidden
 // unit j; the P "parts" p split the columns of the weight gradients and

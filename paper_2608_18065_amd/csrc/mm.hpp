@@ -67,6 +67,43 @@ __device__ inline void store4(double* p, const double (&v)[2]) {
   *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
 }
 
+// sums over lanes 16 and 32 apart, by lane swaps
+__device__ inline float xor16_sum(float v) { return mf16::sum_xor16(v); }
+__device__ inline float xor32_sum(float v) { return mf16::sum_xor32(v); }
+// both halves of a double through the VALU lane swap, as sum_xor16 / sum_xor32
+template <bool ROW> __device__ inline double swap_sum(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+  const auto rl = ROW ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
+                      : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto rh = ROW ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
+                      : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  auto d = [](uint32_t l, uint32_t h) {
+    return __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
+  };
+  return d(rl[0], rh[0]) + d(rl[1], rh[1]);
+}
+__device__ inline double xor16_sum(double v) { return swap_sum<true>(v); }
+__device__ inline double xor32_sum(double v) { return swap_sum<false>(v); }
+// value of the lane that DPP control C names (within rows of 16 lanes)
+template <int C> __device__ inline float row_lane(float v) { return mf16::dpp_f<C>(v); }
+template <int C> __device__ inline double row_lane(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, C, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+// value of lane L (the same in every lane)
+template <int L> __device__ inline float wave_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), L));
+}
+template <int L> __device__ inline double wave_lane(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, L);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), L);
+  return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+
 // workgroup barrier ordering shared memory only; a single wave needs a fence
 template <int NW> __device__ inline void mm_sync() {
   if constexpr (NW == 1) {

@@ -41,28 +41,6 @@
 
 namespace minsr {
 
-namespace {
-
-__device__ inline float xor16_sum(float v) { return mf16::sum_xor16(v); }
-__device__ inline float xor32_sum(float v) { return mf16::sum_xor32(v); }
-// both halves of a double through the VALU lane swap, as sum_xor16 / sum_xor32
-template <bool ROW> __device__ inline double swap_sum(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
-  const auto rl = ROW ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
-                      : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto rh = ROW ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
-                      : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  auto d = [](uint32_t l, uint32_t h) {
-    return __longlong_as_double((long long)(((unsigned long long)h << 32) | l));
-  };
-  return d(rl[0], rh[0]) + d(rl[1], rh[1]);
-}
-__device__ inline double xor16_sum(double v) { return swap_sum<true>(v); }
-__device__ inline double xor32_sum(double v) { return swap_sum<false>(v); }
-
-}  // namespace
-
 // RM_ELOC_SPLIT: FP32 2D local energies with the gate products as FP16 hi/lo
 // pairs and the hardware exp2 and reciprocal in the cell, both as the 1D local
 // energies have them (gru_mfma.hip); the h' product stays FP32
