@@ -428,10 +428,11 @@ __global__ __launch_bounds__(256, 2) void k_jac_rows_mm(JmArgs<T> a) {
   constexpr int TB = M::TB, KS = 64 / TB;              // sites per K-step
   constexpr int WT = H / TB >= 4 ? 2 : 1;              // tiles per side of a wave's block
   constexpr int NB = H < TB ? 1 : H / (TB * WT);       // blocks per side
-  constexpr bool PAD = H < TB;                         // a tile wider than the model
   constexpr int NM = DIM == 2 ? 5 : 3, NG = DIM == 2 ? 5 : 4;
   constexpr int ds = DIM == 1 ? 2 : 4;
-  constexpr int UB = 8;                                // K-steps requested together
+  constexpr bool PAD = H < TB;                         // a tile wider than the model
+  constexpr int UB = PAD ? 3 : 8;                      // K-steps requested together (d_h = 8, 36
+                                                       // sites, 2048 rows: 8 47 us, 5 41.5, 3 40.6)
   extern __shared__ __align__(16) unsigned char rsm[];
   T* dz = reinterpret_cast<T*>(rsm);                   // [N][2] head adjoints
   int16_t* pre = reinterpret_cast<int16_t*>(dz + 2 * a.N);   // [3][N] the site, its predecessors, -1: none
