@@ -504,6 +504,27 @@ __global__ __launch_bounds__(TBS) void k_dc_init(DcArgs a) {
 
 constexpr int DCB = 1024;   // workgroup of the per-node kernels
 
+// sum of v over the lower threads of a DCB workgroup, and over all of it
+__device__ int block_before(int v, int* wsum, int& total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    const int y = __shfl_up(x, m, 64);
+    if (lane >= m) x += y;
+  }
+  __syncthreads();
+  if (lane == 63) wsum[wv] = x;
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int i = 0; i < DCB / 64; ++i) {
+    before += i < wv ? wsum[i] : 0;
+    all += wsum[i];
+  }
+  total = all;
+  return before + x - v;
+}
+
 // Ascending order of every node's children's eigenvalues (ties by index), one
 // entry per thread: m compares each, on as many compute units as there are 64
 // entries (inside k_dc_prep, on one: 1.1 of its 1.55 ms at 4096 entries).
@@ -538,6 +559,8 @@ __global__ __launch_bounds__(64) void k_dc_rank(DcArgs a, int lev) {
 __global__ __launch_bounds__(DCB) void k_dc_prep(DcArgs a, int lev) {
   extern __shared__ double sm[];
   __shared__ double red[DCB / 64];
+  __shared__ uint64_t flags[PINV_MAX_N / 64];
+  __shared__ int wsum[DCB / 64];
   __shared__ int sK, sR;
   const int n = a.n, tid = threadIdx.x, slot = blockIdx.x;
   int lo, m;
@@ -581,40 +604,74 @@ __global__ __launch_bounds__(DCB) void k_dc_prep(DcArgs a, int lev) {
   }
   mx = block_max(mx, red);
   const double tol = 8.0 * 2.220446049250313e-16 * mx;
-  // deflation scan (sequential)
+  // Deflation, as a scan over the entries in order: entries of small z are
+  // dropped, and of two neighbours left that are close the first one is rotated
+  // away.  Whether unrotated neighbours are close is decided in parallel; one
+  // thread follows only the chains of rotations (in a scan by one thread every
+  // entry waited for its root and divisions: 4096 entries 880 us, now 29).
+  auto close = [&](int pa, int pb, double& tt, double& c_, double& s_) {
+    s_ = sz[pa];
+    c_ = sz[pb];
+    tt = hypot(c_, s_);
+    const double t = sd[pb] - sd[pa];
+    c_ /= tt; s_ = -s_ / tt;
+    return fabs(t * c_ * s_) <= tol;
+  };
+  int* left = reinterpret_cast<int*>(s3);      // [m] entries left, in order
+  int* gone = left + m;                        // [m] rotated away
+  const int ch = (m + DCB - 1) / DCB, i0 = min(tid * ch, m), i1 = min(i0 + ch, m);
+  int cnt = 0, S;
+  for (int i = i0; i < i1; ++i) cnt += !(rho * fabs(sz[i]) <= tol);
+  const int first = block_before(cnt, wsum, S);
+  for (int i = i0, at = first; i < i1; ++i)
+    if (!(rho * fabs(sz[i]) <= tol)) { left[at] = i; gone[at] = 0; ++at; }
+  __syncthreads();
+  for (int q0 = 0; q0 < S; q0 += DCB) {
+    const int q = q0 + tid;
+    double tt, c_, s_;
+    const uint64_t bits = __ballot(q + 1 < S && close(left[min(q, S - 1)], left[min(q + 1, S - 1)], tt, c_, s_));
+    if ((tid & 63) == 0) flags[q >> 6] = bits;
+  }
+  __syncthreads();
   if (tid == 0) {
-    int K = 0, nd = 0, nr = 0, pj = -1;
-    // deflated positions are collected from the top of wpos downwards and
-    // reversed afterwards, so wpos = [non-deflated ..., deflated ...]
-    for (int nj = 0; nj < m; ++nj) {
-      if (rho * fabs(sz[nj]) <= tol) { wpos[m - 1 - nd] = nj; ++nd; continue; }
-      if (pj < 0) { pj = nj; continue; }
-      double s_ = sz[pj], c_ = sz[nj];
-      const double tt = hypot(c_, s_);
-      const double t = sd[nj] - sd[pj];
-      c_ /= tt; s_ = -s_ / tt;
-      if (fabs(t * c_ * s_) <= tol) {
-        sz[nj] = tt; sz[pj] = 0.0;
-        rotp[nr] = pj; rotn[nr] = nj; rotc[nr] = c_; rots[nr] = s_; ++nr;
-        const double dp = sd[pj], dn = sd[nj];
-        sd[pj] = dp * c_ * c_ + dn * s_ * s_;
-        sd[nj] = dp * s_ * s_ + dn * c_ * c_;
-        wpos[m - 1 - nd] = pj; ++nd;
-        pj = nj;
-      } else {
-        wpos[K++] = pj;
-        pj = nj;
+    int nr = 0, cur = 0;
+    for (int wd = 0; 64 * wd < S; ++wd)
+      for (uint64_t bits = flags[wd]; bits; bits &= bits - 1) {
+        int e = 64 * wd + __builtin_ctzll(bits);
+        if (e < cur) continue;
+        for (; e + 1 < S; ++e) {
+          const int pa = left[e], pb = left[e + 1];
+          double tt, c_, s_;
+          if (!close(pa, pb, tt, c_, s_)) break;
+          sz[pb] = tt; sz[pa] = 0.0;
+          rotp[nr] = pa; rotn[nr] = pb; rotc[nr] = c_; rots[nr] = s_; ++nr;
+          const double dp = sd[pa], dn = sd[pb];
+          sd[pa] = dp * c_ * c_ + dn * s_ * s_;
+          sd[pb] = dp * s_ * s_ + dn * c_ * c_;
+          gone[e] = 1;
+        }
+        cur = e + 1;
       }
-    }
-    if (pj >= 0) wpos[K++] = pj;
-    // deflated entries were stored in reverse scan order
-    for (int a0 = K, b0 = m - 1; a0 < b0; ++a0, --b0) {
-      const int t = wpos[a0]; wpos[a0] = wpos[b0]; wpos[b0] = t;
-    }
-    sK = K; sR = nr;
-    kinfo[2 * slot] = K;
+    sK = S - nr; sR = nr;
+    kinfo[2 * slot] = S - nr;
     kinfo[2 * slot + 1] = nr;
     w.rho[lo] = rho;
+  }
+  __syncthreads();
+  // wpos = [not deflated ..., small z ..., rotated away ...]
+  {
+    const int e0 = min(tid * ch, S), e1 = min(e0 + ch, S);
+    int kept = 0, all;
+    for (int e = e0; e < e1; ++e) kept += !gone[e];
+    int at = block_before(kept, wsum, all);
+    for (int e = e0; e < e1; ++e) {
+      if (gone[e]) wpos[sK + (m - S) + (e - at)] = left[e];
+      else wpos[at++] = left[e];
+    }
+    for (int i = i0, ls = first; i < i1; ++i) {
+      if (ls < S && left[ls] == i) ++ls;
+      else wpos[sK + (i - ls)] = i;
+    }
   }
   __syncthreads();
   const int K = sK, nr = sR;
