@@ -151,7 +151,7 @@ __device__ __host__ inline void node_of(int n, int lev, int slot, int& lo, int& 
 // workgroups as there are rows for, form the scalars redundantly from
 // partial sums, and request every operand before the first wait.  (With the
 // reflector, the panel's dot products and w on one workgroup the two kernels
-// took 9.7 + 10.8 us on average at n = 4096; now 4.0 + 11.2,
+// took 9.7 + 10.8 us on average at n = 4096; now 4.0 + 10.6,
 // and 22 instead of 2 x 19 us for the update of 16 columns.)
 struct TriArgs {
   double *A, *V, *W, *tau, *d, *e, *bq, *y, *s12, *col, *pd, *pn, *pb, *scal;
@@ -159,7 +159,8 @@ struct TriArgs {
 };
 
 constexpr int TBS = 1024;
-constexpr int TMR = 8;                     // rows (wavefronts) of a k_tri_mv workgroup
+constexpr int TMR = 4;                     // rows (wavefronts) of a k_tri_mv workgroup: 4 10.6 us
+                                           // a column of n = 4096, 8 11.0, 16 12.7
 
 // value of lane q (a constant) in every lane
 __device__ __forceinline__ double lane_value(double v, int q) {
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(64) void k_tri_row(TriArgs a, int j, int p, int npd
 // The reflector of column j (position p of its panel) from col, formed by
 // every workgroup: v = col sc with v[j+1] = 1, in LDS.  Then one wavefront a
 // row: y[i] = A[i] . v for i > j; and, as 2p more rows, s1[q] = W_q . v and
-// s2[q] = V_q . v.  nrow workgroups take A's rows, workgroup b rows 8 (rb + b)
+// s2[q] = V_q . v.  nrow workgroups take A's rows, workgroup b rows 4 (rb + b)
 // onwards with rb a multiple of 8: a row stays on the same XCD from column to
 // column, so that trailing matrices within the L2 caches stay there.
 __global__ __launch_bounds__(64 * TMR) void k_tri_mv(TriArgs a, int j, int p, int rb, int nrow,

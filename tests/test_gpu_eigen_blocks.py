@@ -1,5 +1,5 @@
 """Pseudo-inverse at the edges of the tridiagonalisation's panels (16), of its
-workgroups' rows (8, 64) and of the back-transformation's blocks (64)."""
+workgroups' rows (4, 32) and of the back-transformation's blocks (64)."""
 import numpy as np
 import pytest
 import torch
