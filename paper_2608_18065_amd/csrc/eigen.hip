@@ -16,6 +16,7 @@
 // Each merge runs on one workgroup per node for the sequential parts (deflation
 // scan, rotations), on a thread per entry for the order, and on one wavefront
 // per root, entry or column for the secular equations and eigenvectors.
+#include "mm.hpp"
 #include "model.hpp"
 #include <cmath>
 #include <vector>
@@ -102,11 +103,9 @@ static PinvWs carve(double* base, int n, int nmax) {
 }
 
 // ------------------------------------------------------------ helpers
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
+// (an xor butterfly's sums without its round trips through the shared-memory
+// crossbar: every kernel here waits for one to three of them in a row)
+__device__ __forceinline__ double wave_sum(double v) { return unit_sum<64>(v); }
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v = fmax(v, __shfl_xor(v, m, 64));
@@ -151,7 +150,7 @@ __device__ __host__ inline void node_of(int n, int lev, int slot, int& lo, int& 
 // workgroups as there are rows for, form the scalars redundantly from
 // partial sums, and request every operand before the first wait.  (With the
 // reflector, the panel's dot products and w on one workgroup the two kernels
-// took 9.7 + 10.8 us on average at n = 4096; now 4.0 + 10.6,
+// took 9.7 + 10.8 us on average at n = 4096; now 3.8 + 10.3,
 // and 22 instead of 2 x 19 us for the update of 16 columns.)
 struct TriArgs {
   double *A, *V, *W, *tau, *d, *e, *bq, *y, *s12, *col, *pd, *pn, *pb, *scal;

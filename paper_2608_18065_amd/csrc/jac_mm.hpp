@@ -56,25 +56,6 @@ template <typename T> struct JmArgs {
 };
 
 // ------------------------------------------------------------ output head
-// sum over groups of W lanes in every lane, in the order of an xor butterfly
-// from W / 2 down (W = 8: up), on the VALU: a row's values repeat with the
-// distances already added, so a rotation reaches the partner's value
-template <int W, typename T> __device__ inline T unit_sum(T v) {
-  if constexpr (W == 64) v = xor32_sum(v);
-  if constexpr (W >= 32) v = xor16_sum(v);
-  if constexpr (W >= 16) {
-    v += row_lane<0x128>(v);                // rotated by 8
-    v += row_lane<0x124>(v);
-    v += row_lane<0x122>(v);
-    v += row_lane<0x121>(v);
-  } else {
-    v += row_lane<0xB1>(v);                 // quad_perm [1, 0, 3, 2]
-    v += row_lane<0x4E>(v);                 // quad_perm [2, 3, 0, 1]
-    v += row_lane<0x141>(v);                // row_half_mirror
-  }
-  return v;
-}
-
 // one wave per PW (sample, site) pairs: per pair the sums over the units as
 // k_jacobian forms them (an xor butterfly over 64 lanes, then the two
 // wavefronts' halves at d_h = 128), then lane i the conditional of pair i.

@@ -93,6 +93,24 @@ template <int C> __device__ inline double row_lane(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C, 0xF, 0xF, false);
   return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
 }
+// sum over groups of W lanes in every lane, in the order of an xor butterfly
+// from W / 2 down (W = 8: up), on the VALU: a row's values repeat with the
+// distances already added, so a rotation reaches the partner's value
+template <int W, typename T> __device__ inline T unit_sum(T v) {
+  if constexpr (W == 64) v = xor32_sum(v);
+  if constexpr (W >= 32) v = xor16_sum(v);
+  if constexpr (W >= 16) {
+    v += row_lane<0x128>(v);                // rotated by 8
+    v += row_lane<0x124>(v);
+    v += row_lane<0x122>(v);
+    v += row_lane<0x121>(v);
+  } else {
+    v += row_lane<0xB1>(v);                 // quad_perm [1, 0, 3, 2]
+    v += row_lane<0x4E>(v);                 // quad_perm [2, 3, 0, 1]
+    v += row_lane<0x141>(v);                // row_half_mirror
+  }
+  return v;
+}
 // value of lane L (the same in every lane)
 template <int L> __device__ inline float wave_lane(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), L));
