@@ -806,7 +806,6 @@ static void gram_plan(int npairs, size_t Np, size_t ld, int dtype, int want_spli
       if (cost < best * (1.0 - 1e-9)) { best = cost; want = q; }
     }
   }
-  if (dtype == MINSR_F64 && want_split <= 0) want = f64_split(npairs, Np);
   S = pick_split(npairs, Np, want, dtype == MINSR_F64);
   const size_t kgran = dtype == MINSR_F32 ? FK : 64;
   kchunk = (ld + S - 1) / S;
@@ -847,9 +846,20 @@ int launch_gram(int n, size_t Np, const void* R, int dtype, double* T, float* gp
   const int npairs = nt * (nt + 1) / 2;
   int S = 0;
   size_t kchunk = 0;
-  gram_plan(npairs, Np, ld, dtype, want_split, S, kchunk);
-  const size_t need = (size_t)S * npairs * tile * tile * (dtype == MINSR_F32 ? 4 : 8);
-  if (need > gpart_elems * sizeof(float)) return fail(MINSR_E_SHAPE, "Gram workspace too small");
+  const size_t pass = (size_t)npairs * tile * tile * (dtype == MINSR_F32 ? 4 : 8);
+  const size_t room = gpart_elems * sizeof(float);
+  // FP64: no more K ranges than the workspace holds (it is sized for the
+  // model's most rows, and a call of fewer can have more tiles in its split:
+  // 484 columns: at most 2560 rows 5 ranges of 820 tiles, 2496 rows 6 of 780)
+  if (dtype == MINSR_F64) {
+    const int most = (int)std::min<size_t>(MAX_SPLIT, room / pass);
+    int want = want_split > 0 ? want_split : f64_split(npairs, Np);
+    if (want > most) want = std::max(1, most);
+    gram_plan(npairs, Np, ld, dtype, want, S, kchunk);
+  } else {
+    gram_plan(npairs, Np, ld, dtype, want_split, S, kchunk);
+  }
+  if (S * pass > room) return fail(MINSR_E_SHAPE, "Gram workspace too small");
   dim3 grid((unsigned)npairs, (unsigned)S);
   dim3 rgrid((unsigned)((tile / 32) * (tile / 32)), (unsigned)npairs);
   if (dtype == MINSR_BF16) {
