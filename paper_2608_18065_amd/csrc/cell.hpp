@@ -74,8 +74,12 @@ __device__ inline double d_tanh(double x) {
   const double z = copysign(fma(fma(-q, d, h) + fma(-q, dl, l), y, q), x);
   return x != x ? x : z;
 }
+// (below -690 the logistic function is e^x to 1e-299, and e^-x would leave the
+// reciprocal's range)
 __device__ inline double d_sigmoid(double x) {
-  const double t = rcp_newton(1.0 + exp_clamped(fmax(fmin(-x, 708.0), -746.0)));
+  const bool low = x < -690.0;
+  const double e = exp_clamped(fmax(low ? x : -x, -746.0));
+  const double t = low ? e : rcp_newton(1.0 + e);
   return x != x ? x : t;
 }
 // log(1 + e) for 0 <= e <= 1: with 1 + f = 1 + e, or (1 + e) / 2 from e = 1/2
