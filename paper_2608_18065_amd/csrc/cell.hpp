@@ -22,7 +22,7 @@ __device__ inline float d_sigmoid(float x) { return 1.f / (1.f + d_exp(-x)); }
 // 130 instructions a unit.  Mean and largest error in units in the last place
 // over 4e6 arguments against 80-bit values, in brackets the library's: exp
 // 0.250, 0.64 (0.256, 0.88); logistic 0.378, 2.38 (0.381, 2.38); tanh 0.160,
-// 0.86 (0.161, 0.86); log1p 0.204, 0.71 (0.204, 0.63).  NaN arguments give NaN.
+// 0.86 (0.161, 0.86); log1p 0.204, 0.60 (0.204, 0.63).  NaN arguments give NaN.
 
 // e^r - 1 = r + t, x = k ln 2 + r; t holds r's rounding error too
 __device__ inline void exp_parts(double x, double& k, double& r, double& t) {
@@ -89,7 +89,8 @@ __device__ inline double d_sigmoid(double x) {
 __device__ inline double d_log1p(double e) {
   const bool big = e >= 0.5;
   const double f = big ? 0.5 * (e - 1.0) : e;
-  const double s = f * rcp_newton(2.0 + f), z = s * s;
+  const double d = 2.0 + f, dl = f - (d - 2.0), y = rcp_newton(d), q = f * y;
+  const double s = fma(fma(-q, dl, fma(-q, d, f)), y, q), z = s * s;
   double p = 2.0 / 23.0;
   p = fma(p, z, 2.0 / 21.0);
   p = fma(p, z, 2.0 / 19.0);
@@ -101,11 +102,11 @@ __device__ inline double d_log1p(double e) {
   p = fma(p, z, 2.0 / 7.0);
   p = fma(p, z, 2.0 / 5.0);
   p = fma(p, z, 2.0 / 3.0);
-  const double g = 0.5 * f;
+  const double g = 0.5 * f, h = g * f, hl = fma(g, f, -h);
   const double l2 = big ? 0.69314718055994530942 : 0.0, l2l = big ? 2.3190468138462995584e-17 : 0.0;
   const double a = l2 + f, al = f - (a - l2);
   const double b = fma(-g, f, a), bl = fma(-g, f, a - b);
-  return b + fma(s, fma(p, z, g * f), bl + (al + l2l));
+  return b + fma(s, h, fma(s, fma(p, z, hl), bl + (al + l2l)));
 }
 
 }  // namespace minsr
