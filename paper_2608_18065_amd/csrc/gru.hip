@@ -297,9 +297,15 @@ template <int H> struct GroupReduce {
 };
 
 // EVAL: mode 1 with one sequence per group (conditionals and spins handled in
-// batches, below)
-template <typename T, int H, int DIM, int R, bool EVAL = false>
-__global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
+// batches, below); TAPE: a 2D model's gate tape is written.  Its stores in every
+// 2D launch cost the four-sequence form 15 to 19 % of a pass without a tape
+// (d_h = 32, 6 x 5), the one-sequence form of d_h = 128 about 1 %.
+// FP64 of 32 and 64 units with four sequences is held to the 256 registers of
+// two waves a SIMD (local energies, 16 x 2, d_h = 64, 200 samples: 2459 us with
+// 269 registers, 1552 with 256).
+template <typename T, int H, int DIM, int R, bool EVAL = false, bool TAPE = false>
+__global__ __launch_bounds__(256, sizeof(T) == 8 && R == 4 && (H == 32 || H == 64) ? 2 : 1)
+void k_forward(FwdArgs<T> a) {
   using VT = typename VecT<T>::type;
   constexpr int V = VecT<T>::V;
   constexpr int NT = 256;
@@ -437,24 +443,24 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
 
     // log-conditionals and phases from the head sums, nu and nd of the
     // earlier spins being 0 and 1
-    auto conditional = [&](T z0, T z1, T q0, T q1, int nu, int nd, T& lp0, T& lp1, T& ph0, T& ph1) {
+    struct Cond { T lp0, lp1, ph0, ph1; };
+    auto conditional = [&](const T& z0, const T& z1, const T& q0, const T& q1, const int& nu, const int& nd) {
       const T zz0 = z0 + c0, zz1 = z1 + c1;
       const T mx = zz0 > zz1 ? zz0 : zz1;
       const T d = zz0 > zz1 ? zz1 - zz0 : zz0 - zz1;   // -|z0 - z1|
       const T lse = mx + d_log1p(d_exp(d));
-      lp0 = zz0 - lse;
-      lp1 = zz1 - lse;
+      Cond r{zz0 - lse, zz1 - lse, (T)0, (T)0};
       if (a.zero_mag) {
         const int half = N / 2;
-        if (nu >= half) { lp0 = -INFINITY; lp1 = (T)0; }
-        else if (nd >= half) { lp0 = (T)0; lp1 = -INFINITY; }
+        if (nu >= half) { r.lp0 = -INFINITY; r.lp1 = (T)0; }
+        else if (nd >= half) { r.lp0 = (T)0; r.lp1 = -INFINITY; }
       }
-      ph0 = ph1 = (T)0;
       if (a.cplx) {
         const T aa0 = q0 + cp0, aa1 = q1 + cp1;
-        ph0 = PI * aa0 / ((T)1 + fabs(aa0));
-        ph1 = PI * aa1 / ((T)1 + fabs(aa1));
+        r.ph0 = PI * aa0 / ((T)1 + fabs(aa0));
+        r.ph1 = PI * aa1 / ((T)1 + fabs(aa1));
       }
+      return r;
     };
     // evaluation, one sequence per group: conditionals and spins are handled
     // GB sites at a time (the load of the next spin and the conditional lay in
@@ -622,11 +628,12 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
         if (a.mode != MODE_ELOC && a.states && act[r] &&
             ((k + 1) % a.store_every == 0 || DIM == 2))
           a.states[((size_t)s * N + k) * H + j] = hn[r];
-        if (a.mode != MODE_ELOC && a.gates && act[r]) {
-          T* gk = a.gates + ((size_t)s * N + k) * (DIM == 1 ? 4 : 5) * H;
-          gk[j] = gu[r]; gk[H + j] = gr[r]; gk[2 * H + j] = ag[r]; gk[3 * H + j] = gt[r];
-          if (DIM == 2) gk[4 * H + j] = hin_own[r];
-        }
+        if constexpr (DIM == 1 || TAPE)
+          if (a.mode != MODE_ELOC && a.gates && act[r]) {
+            T* gk = a.gates + ((size_t)s * N + k) * (DIM == 1 ? 4 : 5) * H;
+            gk[j] = gu[r]; gk[H + j] = gr[r]; gk[2 * H + j] = ag[r]; gk[3 * H + j] = gt[r];
+            if (DIM == 2) gk[4 * H + j] = hin_own[r];
+          }
       }
       // output head: logits (and phase pre-activations) of every sequence
       T z0[R], z1[R], q0[R], q1[R];
@@ -687,9 +694,8 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
             const int v = (int)(smask >> li) & 1;
             const uint64_t valid = cnt >= 64 ? ~0ull : (1ull << cnt) - 1;
             const int before = __popcll(~smask & valid & ((1ull << li) - 1));
-            T lp0, lp1, ph0, ph1;
-            conditional(keep[0], keep[1], keep[2], keep[3], nup[0] + before, kb + li - nup[0] - before,
-                        lp0, lp1, ph0, ph1);
+            const auto [lp0, lp1, ph0, ph1] = conditional(keep[0], keep[1], keep[2], keep[3], nup[0] + before,
+                                                          kb + li - nup[0] - before);
             const double lpv = (double)(v == 0 ? lp0 : lp1), phv = (double)(v == 0 ? ph0 : ph1);
             const int base = (tid & 63) - li;
             for (int i = 0; i < cnt; ++i) {         // in site order
@@ -714,8 +720,7 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
         if constexpr (can_defer)
           if (defer) continue;
         const int s = sidx[r];
-        T lp0, lp1, ph0, ph1;
-        conditional(z0[r], z1[r], q0[r], q1[r], nup[r], ndn[r], lp0, lp1, ph0, ph1);
+        const auto [lp0, lp1, ph0, ph1] = conditional(z0[r], z1[r], q0[r], q1[r], nup[r], ndn[r]);
         int v;
         if (a.mode == MODE_SAMPLE) {
           double u;
@@ -781,9 +786,18 @@ __global__ __launch_bounds__(256) void k_forward(FwdArgs<T> a) {
 
 template <typename T, int H, int DIM, int R>
 static int launch_fwd_t(const FwdArgs<T>& a, unsigned grid, hipStream_t s) {
-  if (R == 1 && H <= 64 && a.mode == MODE_EVAL)
-    k_forward<T, H, DIM, R, R == 1 && H <= 64><<<grid, 256, 0, s>>>(a);
-  else k_forward<T, H, DIM, R><<<grid, 256, 0, s>>>(a);
+  constexpr bool EV = R == 1 && H <= 64;
+  // models whose Jacobian reads a 2D tape
+  constexpr bool TP = DIM == 2 && (sizeof(T) == 4 ? H >= 32 : H <= 64);
+  const bool ev = EV && a.mode == MODE_EVAL;
+  if (TP && a.gates) {
+    if (ev) k_forward<T, H, DIM, R, EV, TP><<<grid, 256, 0, s>>>(a);
+    else k_forward<T, H, DIM, R, false, TP><<<grid, 256, 0, s>>>(a);
+  } else if (ev) {
+    k_forward<T, H, DIM, R, EV><<<grid, 256, 0, s>>>(a);
+  } else {
+    k_forward<T, H, DIM, R><<<grid, 256, 0, s>>>(a);
+  }
   MINSR_CHECK_LAUNCH();
   return MINSR_OK;
 }
