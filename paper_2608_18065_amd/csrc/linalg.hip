@@ -640,11 +640,16 @@ __global__ __launch_bounds__(256, 2) void k_gram_f64(const double* R, int n, siz
 // rows, whole lines, so the operands come straight from L2; two buffers of 16
 // rows, the next one requested without a condition (clamped at the end), so
 // the wait before a buffer's products leaves the other's loads in flight
-template <typename TR>
+// (ONE: one range of all rows, whose tile goes to S and mirrored itself.  As
+// runs of partial tiles through the workspace of a model of few samples the
+// whole call took, us: 6 x 6, d_h = 16, 16 samples 328, now 218; chain of 20,
+// d_h = 64, 64 samples 2944, now 914; FP32 chain of 30, d_h = 16, one sample
+// 219, now 147)
+template <typename TR, bool ONE>
 __global__ __launch_bounds__(256, 2) void k_param_gram(const TR* R, size_t ld, int rows,
-                                                       int kchunk, double* part, int pair0) {
+                                                       int kchunk, double* out, int Np) {
   int ti, tj;
-  pair_decode(pair0 + blockIdx.x, ti, tj);
+  pair_decode(blockIdx.x, ti, tj);
   const int k0 = blockIdx.y * kchunk, k1 = min(rows, k0 + kchunk);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cl = lane & 15, q = lane >> 4;
@@ -678,14 +683,33 @@ __global__ __launch_bounds__(256, 2) void k_param_gram(const TR* R, size_t ld, i
       f64_products(xb, yb, acc);
     }
   }
-  f64_store_tile(part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * VT_ * VT_, acc, w, lane);
+  if constexpr (ONE) {
+    // lower triangle and its mirror, both as rows
+    __shared__ double t[VT_ * VT_ + VT_];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          t[(32 * (w >> 1) + 16 * i + q + 4 * v) * (VT_ + 1) + 32 * (w & 1) + 16 * j + cl] = acc[i][j][v];
+    __syncthreads();
+    for (int e = threadIdx.x; e < VT_ * VT_; e += 256) {
+      const int a = e / VT_, b = e % VT_;
+      const int i = ti * VT_ + a, j = tj * VT_ + b;
+      if (i < Np && j <= i) out[(size_t)i * Np + j] = t[a * (VT_ + 1) + b];
+      const int im = tj * VT_ + a, jm = ti * VT_ + b;
+      if (jm < Np && im < jm) out[(size_t)im * Np + jm] = t[b * (VT_ + 1) + a];
+    }
+  } else {
+    f64_store_tile(out + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * VT_ * VT_, acc, w, lane);
+  }
 }
 
 // sum the split-K partials in split order; write T (lower and mirror)
 template <typename TA, typename TT>
 __device__ __forceinline__ void gram_reduce_tile(const TA* part, int npairs, int nsplit,
-                                                 int tile, int n, TT* T, int pair, int sub,
-                                                 int pair0 = 0) {
+                                                 int tile, int n, TT* T, int pair, int sub) {
   // one 32 x 32 sub-tile per workgroup: partials summed in split order, the
   // tile written row-wise and its mirror through a shared-memory transpose,
   // so both stores are coalesced rows
@@ -694,7 +718,7 @@ __device__ __forceinline__ void gram_reduce_tile(const TA* part, int npairs, int
   const int sr = sub / nsub, sc = sub % nsub;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   int ti, tj;
-  pair_decode(pair0 + pair, ti, tj);
+  pair_decode(pair, ti, tj);
   // partials summed in split order, eight splits' loads in flight
   TA s[4] = {(TA)0, (TA)0, (TA)0, (TA)0};
   for (int k0 = 0; k0 < nsplit; k0 += 8) {
@@ -731,8 +755,8 @@ __device__ __forceinline__ void gram_reduce_tile(const TA* part, int npairs, int
 
 template <typename TA, typename TT>
 __global__ __launch_bounds__(256) void k_gram_reduce(const TA* part, int npairs, int nsplit,
-                                                     int tile, int n, TT* T, int pair0 = 0) {
-  gram_reduce_tile<TA, TT>(part, npairs, nsplit, tile, n, T, blockIdx.y, blockIdx.x, pair0);
+                                                     int tile, int n, TT* T) {
+  gram_reduce_tile<TA, TT>(part, npairs, nsplit, tile, n, T, blockIdx.y, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_gram_reduce_grouped(const GramJob* jobs, int njobs) {
@@ -894,30 +918,35 @@ int launch_gram(int n, size_t Np, const void* R, int dtype, double* T, float* gp
 
 // S = R^T R over `rows` rows of R (row stride ld, zero columns past Np), exactly
 // symmetric: tiles over the lower triangle, each split over the rows as far as
-// the partial-tile workspace holds, then reduced and mirrored as the Gram's
+// the partial-tile workspace holds, then reduced and mirrored as the Gram's;
+// where that is one range, the product writes S itself
+template <typename TR>
+static int param_gram_t(const TR* R, int rows, int Np, size_t ld, double* S, double* part,
+                        size_t room, hipStream_t s) {
+  const int nt = (Np + VT_ - 1) / VT_, npairs = nt * (nt + 1) / 2;
+  const int split = (int)std::min((size_t)f64_split(npairs, (size_t)rows),
+                                  room / ((size_t)VT_ * VT_ * 8 * npairs));
+  if (split <= 1) {
+    k_param_gram<TR, true><<<(unsigned)npairs, 256, 0, s>>>(R, ld, rows, rows, S, Np);
+    MINSR_CHECK_LAUNCH();
+    return MINSR_OK;
+  }
+  int kchunk = (rows + split - 1) / split;
+  kchunk = (kchunk + 2 * VK - 1) / (2 * VK) * 2 * VK;
+  k_param_gram<TR, false><<<dim3((unsigned)npairs, (unsigned)split), 256, 0, s>>>(R, ld, rows, kchunk, part, Np);
+  MINSR_CHECK_LAUNCH();
+  k_gram_reduce<double, double><<<dim3(4, (unsigned)npairs), 256, 0, s>>>(part, npairs, split, VT_, Np, S);
+  MINSR_CHECK_LAUNCH();
+  return MINSR_OK;
+}
+
 int launch_param_gram(const void* R, int r_f64, int rows, int Np, size_t ld, double* S,
                       float* gpart, size_t gpart_elems, hipStream_t s) {
   if (Np <= 0) return MINSR_OK;
-  const int nt = (Np + VT_ - 1) / VT_, npairs = nt * (nt + 1) / 2;
-  const size_t tile_bytes = (size_t)VT_ * VT_ * 8, room = gpart_elems * sizeof(float);
   double* part = reinterpret_cast<double*>(gpart);
-  size_t split = (size_t)f64_split(npairs, (size_t)rows);
-  split = std::min(split, room / (tile_bytes * npairs));
-  // too many tiles for one pass of the workspace: runs of tiles, one K range
-  const int run = split >= 1 ? npairs : (int)std::max<size_t>(1, room / tile_bytes);
-  if (split < 1) split = 1;
-  int kchunk = (rows + (int)split - 1) / (int)split;
-  kchunk = (kchunk + 2 * VK - 1) / (2 * VK) * 2 * VK;
-  for (int p0 = 0; p0 < npairs; p0 += run) {
-    const int np = std::min(run, npairs - p0);
-    const dim3 grid((unsigned)np, (unsigned)split);
-    if (r_f64) k_param_gram<double><<<grid, 256, 0, s>>>((const double*)R, ld, rows, kchunk, part, p0);
-    else k_param_gram<float><<<grid, 256, 0, s>>>((const float*)R, ld, rows, kchunk, part, p0);
-    MINSR_CHECK_LAUNCH();
-    k_gram_reduce<double, double><<<dim3(4, (unsigned)np), 256, 0, s>>>(part, np, (int)split, VT_, Np, S, p0);
-    MINSR_CHECK_LAUNCH();
-  }
-  return MINSR_OK;
+  const size_t room = gpart_elems * sizeof(float);
+  return r_f64 ? param_gram_t((const double*)R, rows, Np, ld, S, part, room, s)
+               : param_gram_t((const float*)R, rows, Np, ld, S, part, room, s);
 }
 
 // ============================================================= Cholesky
