@@ -21,16 +21,29 @@ __device__ inline float d_sigmoid(float x) { return 1.f / (1.f + d_exp(-x)); }
 // the leading sums and quotients with their rounding errors carried: about
 // 130 instructions a unit.  Mean and largest error in units in the last place
 // over 4e6 arguments against 80-bit values, in brackets the library's: exp
-// 0.250, 0.64 (0.256, 0.88); logistic 0.378, 2.38 (0.381, 2.38); tanh 0.160,
-// 0.86 (0.161, 0.86); log1p 0.204, 0.60 (0.204, 0.63).  NaN arguments give NaN.
+// 0.249, 0.64 (0.256, 0.88); logistic 0.390, 2.36 (0.393, 2.36); tanh 0.203,
+// 0.83 (0.205, 0.86); log1p 0.249, 0.63 (0.252, 0.64).  NaN arguments give NaN.
+//
+// A chain's site waits for every dependent instruction here, so a NaN, a
+// quotient's correction and a scale lie beside the chain where they can.  With
+// a second branch for e^x far below zero, a move for NaN at the end and k by
+// rounding and conversion: chain of 150, d_h = 32, 300 samples 455 us sampling
+// and 389 log psi, now 436 and 372; 6 x 6, d_h = 16, 64 samples log psi 104,
+// now 101.
 
-// e^r - 1 = r + t, x = k ln 2 + r; t holds r's rounding error too
-__device__ inline void exp_parts(double x, double& k, double& r, double& t) {
-  k = rint(x * 1.4426950408889634074);
-  const double x1 = fma(-k, 0x1.62e42feep-1, x);       // exact
+// e^r - 1 = r + t, x = k ln 2 + r; t holds r's rounding error too.  x is within
+// some limits, which drop a NaN: nan says that it was one, and t is then NaN
+// (put back at c, which nothing waits for; a move at the end of a function
+// lay in the chain of every site)
+__device__ inline void exp_parts(double x, bool nan, int& k, double& r, double& t) {
+  const double kb = fma(x, 1.4426950408889634074, 0x1.8p52), kd = kb - 0x1.8p52;
+  k = (int)(uint32_t)__builtin_bit_cast(uint64_t, kb);    // the sum's last word is the integer
+  const double x1 = fma(-kd, 0x1.62e42feep-1, x);      // exact
   const double l2 = 1.9082149292705877e-10;             // the rest of ln 2
-  r = fma(-k, l2, x1);
-  const double c = fma(-k, l2, x1 - r);
+  r = fma(-kd, l2, x1);
+  const uint64_t c0 = __builtin_bit_cast(uint64_t, fma(-kd, l2, x1 - r));
+  const uint32_t ch = nan ? 0x7FF80000u : (uint32_t)(c0 >> 32);   // (one move: the leading word)
+  const double c = __builtin_bit_cast(double, (uint64_t)ch << 32 | (uint32_t)c0);
   double p = 1.0 / 6227020800.0;
   p = fma(p, r, 1.0 / 479001600.0);
   p = fma(p, r, 1.0 / 39916800.0);
@@ -44,53 +57,53 @@ __device__ inline void exp_parts(double x, double& k, double& r, double& t) {
   p = fma(p, r, 1.0 / 6.0);
   t = fma(0.5 * r, r, fma(r * r, r * p, c));
 }
-// 1 / d for 2^-1000 < |d| < 2^1000
+// 1 / d for 2^-1021 <= |d| < 2^1022
 __device__ inline double rcp_newton(double d) {
   double y = __builtin_amdgcn_rcp(d);
   y = fma(fma(-d, y, 1.0), y, y);
   return fma(fma(-d, y, 1.0), y, y);
 }
-// e^x for -746 <= x <= 711 (beyond these the result is 0 or infinite)
-__device__ inline double exp_clamped(double x) {
-  double k, r, t;
-  exp_parts(x, k, r, t);
+// e^x = m 2^k for x within -746 and 746 (at which it is 0 or infinite)
+__device__ inline double exp_mantissa(double x, int& k) {
+  double r, t;
+  exp_parts(fmax(fmin(x, 746.0), -746.0), x != x, k, r, t);
   const double s = 1.0 + r, lo = r - (s - 1.0);
-  return ldexp(s + (lo + t), (int)k);
+  return s + (lo + t);
 }
 __device__ inline double d_exp(double x) {
-  const double e = exp_clamped(fmax(fmin(x, 711.0), -746.0));
-  return x != x ? x : e;
+  int k;
+  const double m = exp_mantissa(x, k);
+  return ldexp(m, k);
 }
 __device__ inline double d_tanh(double x) {
-  double k, r, t;
-  exp_parts(fmin(2.0 * fabs(x), 44.0), k, r, t);                // tanh(22) rounds to 1
+  int k;
+  double r, t;
+  exp_parts(fmin(2.0 * fabs(x), 44.0), x != x, k, r, t);        // tanh(22) rounds to 1
   // e^2|x| - 1 = h + l
-  const double s = ldexp(1.0, (int)k), a = s - 1.0, b = fma(s, r, a);
+  const double s = ldexp(1.0, k), a = s - 1.0, b = fma(s, r, a);
   const double v = fma(s, t, fma(s, r, a - b));
   const double h = b + v, l = v - (h - b);
   // (h + l) / (h + l + 2)
   const double c = fmax(h, 2.0), d = h + 2.0, dl = (fmin(h, 2.0) - (d - c)) + l;
   const double y = rcp_newton(d), q = h * y;
-  const double z = copysign(fma(fma(-q, d, h) + fma(-q, dl, l), y, q), x);
-  return x != x ? x : z;
+  return copysign(fma(fma(-q, d, h) + fma(-q, dl, l), y, q), x);
 }
-// (below -690 the logistic function is e^x to 1e-299, and e^-x would leave the
-// reciprocal's range)
+// (e^-x = m 2^k past the reciprocal's range: that of m 2^1021, scaled)
 __device__ inline double d_sigmoid(double x) {
-  const bool low = x < -690.0;
-  const double e = exp_clamped(fmax(low ? x : -x, -746.0));
-  const double t = low ? e : rcp_newton(1.0 + e);
-  return x != x ? x : t;
+  int k;
+  const double m = exp_mantissa(-x, k);
+  const int kr = k < 1021 ? k : 1021;
+  return ldexp(rcp_newton(1.0 + ldexp(m, kr)), kr - k);
 }
 // log(1 + e) for 0 <= e <= 1: with 1 + f = 1 + e, or (1 + e) / 2 from e = 1/2
 // (both exact), and s = f / (2 + f), |s| <= 0.2, log(1 + f) = 2 atanh(s) =
 // f - (f^2 / 2 - s (f^2 / 2 + p)), p = 2 s^2 / 3 + 2 s^4 / 5 + ...; the series
-// to s^22 is complete to 1e-18
+// to s^22 is complete to 1e-18 and takes the quotient q before its correction
 __device__ inline double d_log1p(double e) {
   const bool big = e >= 0.5;
   const double f = big ? 0.5 * (e - 1.0) : e;
   const double d = 2.0 + f, dl = f - (d - 2.0), y = rcp_newton(d), q = f * y;
-  const double s = fma(fma(-q, dl, fma(-q, d, f)), y, q), z = s * s;
+  const double s = fma(fma(-q, dl, fma(-q, d, f)), y, q), z = q * q;
   double p = 2.0 / 23.0;
   p = fma(p, z, 2.0 / 21.0);
   p = fma(p, z, 2.0 / 19.0);
@@ -106,7 +119,8 @@ __device__ inline double d_log1p(double e) {
   const double l2 = big ? 0.69314718055994530942 : 0.0, l2l = big ? 2.3190468138462995584e-17 : 0.0;
   const double a = l2 + f, al = f - (a - l2);
   const double b = fma(-g, f, a), bl = fma(-g, f, a - b);
-  return b + fma(s, h, fma(s, fma(p, z, hl), bl + (al + l2l)));
+  const double u = fma(s, h, fma(s, hl, bl + (al + l2l)));
+  return b + fma(s, p * z, u);
 }
 
 }  // namespace minsr
