@@ -186,7 +186,8 @@ static PackArgs pack_args(minsr_model* m) {
   p.o_head = p.o_bias + 4 * H;
   p.o_headb = p.o_head + 4 * H;
   p.o_mw = p.o_headb + 4;
-  const bool mf = !m->f64 && H >= 32;
+  // (2D models whose state window fits shared memory take no such fragments)
+  const bool mf = !m->f64 && H >= 32 && !(L.dim == 2 && rec_f32_fits(m));
   p.ks = (int)H / 2;
   p.kx = L.dim == 1 ? 1 : 2;
   p.nstep = 3 * p.ks + 3 * p.kx;
