@@ -985,9 +985,9 @@ static int eloc_t(minsr_model* m, const Work<T>& w, const minsr_hamiltonian* H, 
     // 2D: the state window in shared memory where it fits (d_h = 128: Lx <= 13);
     // chains of 16 units, too narrow for the FP16 products (40 sites, 256
     // samples, with the evaluation: 108 us, 255 with the vector recurrence)
-    if (!m->f64 && !m->force_vector && rec_f32_fits(m) && (m->dim == 2 ? M <= 1024 : m->H == 16))
+    if (!m->f64 && rec_f32_fits(m) && (m->dim == 2 ? M <= 1024 : m->H == 16))
       rc = launch_rec_eloc_f32(m, H, Ns, sigma, states, site, M, s);
-    else if (!m->f64 && !m->force_vector && eloc_mfma_supported(m))
+    else if (!m->f64 && eloc_mfma_supported(m))
       rc = launch_eloc_mfma(m, H, Ns, sigma, states, site, M, s);
     else if (m->f64 && rec_f64_fits(m) && (m->dim == 1 || M <= 1024))
       rc = launch_rec_eloc_f64(m, H, Ns, sigma, states, site, M, s);

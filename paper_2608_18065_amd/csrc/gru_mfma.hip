@@ -260,11 +260,11 @@ __device__ inline void eloc_end(const ElocMArgs& a, const ElocSeq& e) {
   o[1] = e.mel * x * sin(dim_);
 }
 
-template <int H, int DIM>
-// 1D d_h <= 64: two waves per SIMD (at most 256 registers each); 2D keeps
-// the whole register file for one wave (its split weight fragments, the
-// gate-input product and the window of neighbour states)
-__global__ __launch_bounds__(64 * (H / 32), (H <= 64 && DIM == 1) ? 2 : 1) void k_eloc_mfma(ElocMArgs a) {
+// d_h = 128.  One wave a SIMD: split weight fragments, in 2D the gate-input
+// product and the window of neighbour states take its whole register file
+template <int DIM>
+__global__ __launch_bounds__(256, 1) void k_eloc_mfma(ElocMArgs a) {
+  constexpr int H = 128;
   constexpr int S = 32;
   constexpr int HP = H + 4;
   constexpr int KS = H / 2;
@@ -953,13 +953,10 @@ int launch_eloc_mfma(minsr_model* m, const minsr_hamiltonian* H, int Ns, const u
     if (cap < 1) return fail(MINSR_E_SHAPE, "recompute window too small");
     grid = std::min<unsigned>(grid, (unsigned)cap);
   }
-  const unsigned nt = 64u * (unsigned)(m->H / 32);
-#define MINSR_ELOC_MFMA(HH, DD) k_eloc_mfma<HH, DD><<<grid, nt, 0, s>>>(a)
-  // 2D comes here only where the window of states does not fit shared memory
-  if (m->H != 128) return fail(MINSR_E_UNSUPPORTED, "more than 1024 exchange terms");
-  if (m->dim == 1) MINSR_ELOC_MFMA(128, 1);
-  else MINSR_ELOC_MFMA(128, 2);
-#undef MINSR_ELOC_MFMA
+  // (narrower 2D models: their window of states always fits shared memory)
+  if (m->H != 128) return fail(MINSR_E_UNSUPPORTED, "local energies: hidden width");
+  if (m->dim == 1) k_eloc_mfma<1><<<grid, 256, 0, s>>>(a);
+  else k_eloc_mfma<2><<<grid, 256, 0, s>>>(a);
   MINSR_CHECK_LAUNCH();
   return MINSR_OK;
 }

@@ -71,7 +71,6 @@ struct minsr_model {
   int eig_nmax = 0;         // largest n the eigen workspace serves
   int last_n = 0;
   int last_form = 0;
-  int force_vector = 0;     // testing: route FP32 local energies to the vector kernel
   // launch parameters (0 = built-in choice), set by the autotuner
   int tune_gram_split = 0;
   int tune_eloc_grid = 0;
