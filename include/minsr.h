@@ -426,8 +426,12 @@ int minsr_batch_destroy(minsr_batch* b);
  * matrix-core recurrence (same results bit for bit; FP32 1D chains with
  * d_h = 64 or 128 and N <= 256 sample with split FP16 products, which this
  * key does not affect);
- * key "jac_parts": threads per hidden unit of the Jacobian's reverse pass
- * (1, 2 or 4; d_h = 64 and 128 only; 0 = built-in choice);
+ * key "jac_parts": 0 = built-in choice of the Jacobian's kernels; 1, 2 or 4:
+ * the per-sample kernel at every width, with that many threads per hidden
+ * unit of its reverse pass at d_h = 64 and 128 (one below).  2D models and
+ * FP64 chains then leave the matrix cores (2 to 18 times slower; FP32 rows
+ * keep their bits, FP64 rows differ in their last ones), and the checkpoint
+ * stride takes effect again for FP64 chains;
  * key "solve_spin_limit": polls after which a wait of one workgroup of the
  * Cholesky solve on another gives up (0 = built in, 2^22 polls, of the
  * order of seconds).  A wait that gives up ends every wait of the launch,

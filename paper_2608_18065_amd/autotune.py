@@ -18,7 +18,7 @@ faster by more than timings of the same kernels differ.
     eloc_grid    local-energy recurrence      0 (one per item), 256, 512, 1024, 2048
     sample_r     sampling + an evaluation     0 (built-in), 1, 4 (vector forms; no effect on the
                                               sampling of FP32 chains of 64 or 128 units)
-    jac_parts    Jacobian reverse pass        0 (built-in), 1, 2, 4
+    jac_parts    Jacobian reverse pass        0 (built-in), 1, 2, 4 (the per-sample kernel)
 """
 import json
 import os
