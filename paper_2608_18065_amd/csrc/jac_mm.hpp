@@ -9,7 +9,7 @@
 // those streams).  Here
 //   k_jac_head  forms the output head's conditionals of every site, 64 at a
 //               time per wave, with k_jacobian's reduction order;
-//   k_jac_rev   walks 16 rows at once backwards, with the transposed weights
+//   k_jac_rev_mm walks 16 rows at once backwards, with the transposed weights
 //               in registers as MFMA operands (recur_mm.hpp has the layout): a
 //               site is one [d_h x 3 d_h] x [3 d_h x 16] product for the cell
 //               input's adjoint and, in 2D, one [2 d_h x d_h] x [d_h x 16]
@@ -186,7 +186,7 @@ constexpr size_t jm_rev_smem(int dim, int Lx) {
 }
 
 template <typename T, int H, int DIM, int P>
-__global__ __launch_bounds__(64 * mm_tiles(H), sizeof(T) == 8 && H == 64 ? 1 : 2) void k_jac_rev(JmArgs<T> a) {
+__global__ __launch_bounds__(64 * mm_tiles(H), sizeof(T) == 8 && H == 64 ? 1 : 2) void k_jac_rev_mm(JmArgs<T> a) {
   using M = MM<T>;
   using acc_t = typename M::acc;
   using vec_t = typename M::vec;
@@ -583,7 +583,7 @@ static int jm_chunk(const JmArgs<T>& a, hipStream_t s) {
   static std::once_flag once;   // more than 64 KiB of dynamic shared memory
   hipError_t attr = hipSuccess;
   std::call_once(once, [&] {
-    attr = hipFuncSetAttribute((const void*)k_jac_rev<T, H, DIM, P>,
+    attr = hipFuncSetAttribute((const void*)k_jac_rev_mm<T, H, DIM, P>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)MM_LDS);
   });
   MINSR_HIP(attr);
@@ -592,7 +592,7 @@ static int jm_chunk(const JmArgs<T>& a, hipStream_t s) {
   if (pairs > 65536) k_jac_head<T, H, 64><<<(unsigned)((pairs + 255) / 256), 256, 0, s>>>(a);
   else k_jac_head<T, H, 16><<<(unsigned)((pairs + 63) / 64), 256, 0, s>>>(a);
   MINSR_CHECK_LAUNCH();
-  k_jac_rev<T, H, DIM, P><<<seeds * (unsigned)((a.ns + 15) / 16), 64 * mm_tiles(H),
+  k_jac_rev_mm<T, H, DIM, P><<<seeds * (unsigned)((a.ns + 15) / 16), 64 * mm_tiles(H),
                             jm_rev_smem<T, H, P>(DIM, a.Lx), s>>>(a);
   MINSR_CHECK_LAUNCH();
   k_jac_rows_mm<T, H, DIM><<<seeds * (unsigned)a.ns, 256, a.N * (2 * sizeof(T) + 8), s>>>(a);
