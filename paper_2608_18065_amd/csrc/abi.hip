@@ -74,34 +74,40 @@ static int ensure_pinv_ws(minsr_model* m, hipStream_t s) {
   return MINSR_OK;
 }
 
-// The tapes of the matrix-core Jacobian: what a model can do without, so they
-// come after everything else and take no more than 4 GiB nor a sixteenth of
-// the memory that is still free (further models and the program's own tensors
-// need it); in chunks of samples where all of max_Ns would be more, whole
-// rounds of 16 rows on 256 compute units where it holds that many.  Without
-// them k_jacobian serves the model.
-static void reserve_tapes(minsr_model* m) {
+// The states, and behind them in one block the tapes of the matrix-core
+// Jacobian.  A model can do without the tapes (k_jacobian then serves it), so
+// this comes after every other buffer, and tapes of more than 64 MiB take no
+// more than 4 GiB nor a sixteenth of the memory that is still free (further
+// models and the program's own tensors need it); in chunks of samples where all
+// of max_Ns would be more, whole rounds of 16 rows on 256 compute units where
+// it holds that many.
+static int reserve_states(minsr_model* m) {
   const size_t S = (size_t)m->d.max_Ns, N = (size_t)m->N, H = (size_t)m->H, sz = m->f64 ? 8 : 4;
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-    (void)hipGetLastError();
-    return;
+  const size_t st = S * N * H * sz;
+  if (m->f64 ? jac_mm_f64_fits(m) : jac_mm_f32_fits(m)) {
+    const size_t per = jac_mm_site_elems(m) * N * sz;
+    size_t c = S, free_b = 0, total_b = 0;
+    if (S * per > (size_t)64 << 20) {
+      if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) (void)hipGetLastError();
+      free_b = free_b > st ? free_b - st : 0;
+      c = std::min((size_t)4 << 30, free_b / 16) / per;
+      if (c < S) c = c / 16 * 16;
+      if (c > 4096) c = c / 4096 * 4096;
+      c = std::min(c, S);
+    }
+    const size_t g = c * N * (m->dim == 2 ? 5 : 4) * H * sz, hd = c * N * 4 * sz;
+    if (c > 0 && alloc(&m->states, st + g * (m->cplx ? 3 : 2) + hd) == MINSR_OK) {
+      char* p = (char*)m->states + st;
+      m->gates = p; m->jhead = p + g; m->jadj = p + g + hd;
+      m->gates_ns = (int)c;
+      return MINSR_OK;
+    }
   }
-  const size_t per = jac_mm_site_elems(m) * N * sz;
-  size_t c = std::min((size_t)4 << 30, free_b / 16) / per;
-  if (c < S) c = c / 16 * 16;
-  if (c > 4096) c = c / 4096 * 4096;
-  c = std::min(c, S);
-  if (c == 0) return;
-  const size_t g = c * N * (m->dim == 2 ? 5 : 4) * H * sz, hd = c * N * 4 * sz;
-  if (alloc(&m->gates, g * (m->cplx ? 3 : 2) + hd) != MINSR_OK) return;
-  m->jhead = (char*)m->gates + g;
-  m->jadj = (char*)m->gates + g + hd;
-  m->gates_ns = (int)c;
+  return alloc(&m->states, st);
 }
 
 static void release(minsr_model* m) {
-  void* ptrs[] = {m->theta, m->work, m->nbr, m->subA, m->bonds, m->states, m->gates, m->jdp, m->jtape, m->site,
+  void* ptrs[] = {m->theta, m->work, m->nbr, m->subA, m->bonds, m->states, m->jadj ? nullptr : m->gates, m->jdp, m->jtape, m->site,
                   m->contrib,
                   m->elist, m->ecount, m->eitems, m->eloc_q,
                   m->diag, m->ring, m->sigma, m->logpsi, m->eloc, m->stats, m->O, m->R,
@@ -218,7 +224,6 @@ int minsr_create_model(const minsr_model_desc* d, minsr_model** out) {
   rc = rc ? rc : alloc((void**)&m->nbr, nbr.size() * sizeof(int));
   rc = rc ? rc : alloc((void**)&m->subA, subA.size());
   rc = rc ? rc : alloc((void**)&m->bonds, std::max<size_t>(bonds.size(), 2) * sizeof(int));
-  rc = rc ? rc : alloc(&m->states, S * Nz * Hz * sz);
   // the Jacobian of these models reads the sampler's gate values instead of
   // recomputing them (checkpoint stride 1)
   if (m->dim == 1 && !m->f64 && m->H <= 64) {
@@ -262,8 +267,8 @@ int minsr_create_model(const minsr_model_desc* d, minsr_model** out) {
   rc = rc ? rc : alloc((void**)&m->status, 16);
   rc = rc ? rc : alloc((void**)&m->eloc_q, 16);
   if (!rc && (d->options & MINSR_OPT_PINV)) rc = ensure_pinv_ws(m, nullptr);
+  rc = rc ? rc : reserve_states(m);
   if (rc) { release(m); delete m; return rc; }
-  if (m->f64 ? jac_mm_f64_fits(m) : jac_mm_f32_fits(m)) reserve_tapes(m);
 
   hipError_t e = hipMemcpy(m->nbr, nbr.data(), nbr.size() * sizeof(int), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(m->subA, subA.data(), subA.size(), hipMemcpyHostToDevice);
