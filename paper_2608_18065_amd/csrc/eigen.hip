@@ -608,7 +608,9 @@ __global__ __launch_bounds__(DCB) void k_dc_prep(DcArgs a, int lev) {
   // dropped, and of two neighbours left that are close the first one is rotated
   // away.  Whether unrotated neighbours are close is decided in parallel; one
   // thread follows only the chains of rotations (in a scan by one thread every
-  // entry waited for its root and divisions: 4096 entries 880 us, now 29).
+  // entry waited for its root and divisions: 4096 entries of a random matrix
+  // 880 us, now 29; a step's spectrum has more rotations: 10 x 10, 4096 samples
+  // 0.80 ms over the twelve levels).
   auto close = [&](int pa, int pb, double& tt, double& c_, double& s_) {
     s_ = sz[pa];
     c_ = sz[pb];

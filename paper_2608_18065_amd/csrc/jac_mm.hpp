@@ -7,16 +7,16 @@
 // their transposes from L2 at each site and keeps the whole gradient in
 // registers (10 x 10, d_h = 128, Ns = 4096: 42 ms for 1.4 GB of rows, bound by
 // those streams).  Here
-//   k_jac_head  forms the output head's conditionals of every site, 64 at a
-//               time per wave, with k_jacobian's reduction order;
-//   k_jac_rev_mm walks 16 rows at once backwards, with the transposed weights
-//               in registers as MFMA operands (recur_mm.hpp has the layout): a
-//               site is one [d_h x 3 d_h] x [3 d_h x 16] product for the cell
-//               input's adjoint and, in 2D, one [2 d_h x d_h] x [d_h x 16]
-//               product for the predecessors'; it writes the site's gate
-//               adjoints;
-//   k_jac_rows  one workgroup per row: the weight blocks as [d_h x N] x
-//               [N x d_h] products over the sites, the rest as sums.
+//   k_jac_head    forms the output head's conditionals of every site, 64 at a
+//                 time per wave, with k_jacobian's reduction order;
+//   k_jac_rev_mm  walks 16 rows at once backwards, with the transposed weights
+//                 in registers as MFMA operands (recur_mm.hpp has the layout): a
+//                 site is one [d_h x 3 d_h] x [3 d_h x 16] product for the cell
+//                 input's adjoint and, in 2D, one [2 d_h x d_h] x [d_h x 16]
+//                 product for the predecessors'; it writes the site's gate
+//                 adjoints;
+//   k_jac_rows_mm one workgroup per row: the weight blocks as [d_h x N] x
+//                 [N x d_h] products over the sites, the rest as sums.
 // The MFMAs add their products as ascending fma chains, so the order of
 // k_jacobian's sums is kept by the order of the operands: the reverse product
 // as its partial sums (4 per part of the rows), the weight blocks from the

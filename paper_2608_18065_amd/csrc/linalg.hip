@@ -523,11 +523,12 @@ __global__ __launch_bounds__(256, 2) void k_gram_f32(const float* R, int n, size
 // FP64 products on v_mfma_f64_16x16x4, one 64 x 64 tile over one K range a
 // workgroup, 32 x 32 of it a wave (lane l: A[l % 16][l / 16], B[l / 16][l % 16];
 // result element v in row l / 16 + 4 v).  Bound by the products (64 cycles
-// each); the K ranges fill the chip from few tiles.  us, with the vector
+// each); the K ranges fill the chip from few tiles.  us, in brackets the vector
 // kernels that were here (4 x 4 outputs a thread, no more than eight K ranges
 // of 256, or none): Gram n = 64, 960 columns 11 (52), n = 502, 5764 columns 41
-// (153; 20 at 73 TFLOP/s), n = 1400, 13188 columns 452 (354); parameter-space
-// metric 484 columns, 2048 rows 20 (531).
+// (153; at 73 TFLOP/s it would be 20); with its reduction n = 1400, 13188
+// columns 496 (1351; 353), n = 4000 3905 (10255; 2879); parameter-space metric
+// 484 columns, 2048 rows 20 (531).
 constexpr int VT_ = 64, VK = 16;
 typedef __attribute__((ext_vector_type(4))) double f64x4s;
 

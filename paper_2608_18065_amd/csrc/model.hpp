@@ -34,7 +34,7 @@ struct minsr_model {
   int gates_ns = 0;         // max_Ns, or fewer where the Jacobian works in chunks
   void* jhead = nullptr;    // matrix-core Jacobian: [gates_ns][N][4] output-head conditionals
   void* jadj = nullptr;     //   and [seeds][gates_ns][N][4 or 5][H] gate adjoints
-  void* jdp = nullptr;      // [seeds][max_Ns][N][3][H] gate adjoints of the Jacobian (same models)
+  void* jdp = nullptr;      // [seeds][max_Ns][N][3][H] gate adjoints of the Jacobian (FP32 1D, d_h 32, 64)
   void* jtape = nullptr;    // FP32 1D d_h = 128: [seeds][max_Ns][N][4][H] gate adjoints, then
                             //   [seeds][max_Ns][N][2] head adjoints (matrix-core Jacobian)
   double* site = nullptr;   // [max_Ns][N][4]: log p(0), log p(1), phi(0), phi(1)
@@ -99,8 +99,9 @@ int launch_init_blocks(double* theta, long long Np, const InitBlocks& b, uint64_
 int launch_init_theta(minsr_model* m, hipStream_t s);
 int launch_pack(minsr_model* m, hipStream_t s);
 // mode 0: sample, 1: evaluate.  states/site may be null.
-// gates (1D, store_every == 1, may be null): [Ns][N][4][H] gate values u, r,
-// candidate pre-activation and candidate of every site, for the Jacobian.
+// gates (store_every == 1, may be null): the tape of every site for the
+// Jacobian, 1D [Ns][N][4][H] u, r, candidate pre-activation and candidate, 2D
+// [Ns][N][5][H] with the cell input h' last.
 // sample_mfma.hip: sampling of 1D FP32 models with d_h = 64 or 128 (N <= 256)
 // on the matrix cores; launch_forward takes it for mode 0 where it applies
 bool sample_mfma_supported(const minsr_model* m);
