@@ -885,6 +885,7 @@ int launch_forward(minsr_model* m, int mode, int Ns, const double* uniforms, uin
                    int store_every, double* site, hipStream_t s, const uint64_t* counter_ptr,
                    void* gates, uint32_t* zero_word) {
   if (Ns == 0) return MINSR_OK;
+  if (!jac_reads_tape(m)) gates = nullptr;
   // FP32 chains of 64 or 128 units sample with split FP16 products; the
   // evaluation's arithmetic is the one that the Jacobian's checkpoint
   // recomputation repeats exactly

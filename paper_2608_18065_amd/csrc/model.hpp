@@ -178,6 +178,9 @@ int launch_jac_mm_f64(minsr_model* m, int Ns, const uint8_t* sigma, const void* 
 // whether launch_jacobian takes it: every state is needed and the checkpoint
 // stride has no effect
 inline bool jac_mm(const minsr_model* m) { return m->jadj && m->tune_jac_parts == 0; }
+// whether its kernels read the forward pass's tape (the per-sample one of 2D
+// models forms the gates itself)
+inline bool jac_reads_tape(const minsr_model* m) { return m->dim == 1 || jac_mm(m); }
 // linalg.hip
 // centred (colmean != null) or plain copy of O into R with row stride ldo
 // (ldo >= Np; columns Np..ldo-1 are written as zeros)
